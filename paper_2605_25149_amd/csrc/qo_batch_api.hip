@@ -487,12 +487,12 @@ qo_status build_group(qo_batch_ctx *b, qo_batch_ctx::Group &G) {
     std::vector<int> nsplit(G.ninst);
     for (int li = 0; li < G.ninst; ++li) {
         const int n = b->cfg[G.members[li]].N;
-        // K-chunks per Gram: about 8192 wavefronts over the whole group (the
-        // single-instance rule targets 4096 for one Gram), at least 256 rows each, and the
-        // instance's partials capped like the single-instance ones
+        // K-chunks per Gram: about 2048 four-wavefront workgroups over the whole group, at
+        // least 256 rows each, and the instance's partials capped like the single-instance
+        // ones
         {
             const int np = gram_pairs(n);
-            long ns = 8192 / ((long)np * G.ninst);
+            long ns = 2048 / ((long)np * G.ninst);
             ns = std::min(ns, (G.ng + 255) / 256);
             ns = std::min(ns, (long)gram_nsplit(G.ng, n));
             nsplit[li] = (int)std::max(1L, ns);

@@ -2,10 +2,11 @@
 // inner-product matrices of Sec. 2.1 that the scheme of Sec. 4.1 needs
 // (<U,U>, <U,GU>, <GU,GU> and <U_hat,U_hat>, <U_hat,GU_hat>, <GU_hat,GU_hat>).
 //
-// Split-K over the grid: one wavefront computes one 64x64 tile of the upper
-// block triangle over one chunk of rows with MFMA, writes it as a partial,
-// and a second kernel sums the partials of every entry in a fixed order and
-// mirrors the upper triangle (deterministic, exactly symmetric).
+// Split-K over the grid: a workgroup computes one 64x64 tile of the upper
+// block triangle over one chunk of rows with MFMA (FP64: four wavefronts, a
+// quarter of the rows each, summed through LDS), writes it as a partial, and a
+// second kernel sums the partials of every entry in a fixed order and mirrors
+// the upper triangle (deterministic, exactly symmetric).
 //
 // Operand trick: the sum over grid rows may visit the rows in any order as
 // long as both operands use the same order, so lane l takes rows
@@ -17,6 +18,7 @@
 #include "qo_internal.h"
 #include "qo_device.h"
 
+#include <algorithm>
 #include <type_traits>
 
 
@@ -28,7 +30,9 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
-constexpr int TM = 64;  // output tile edge per wavefront
+constexpr int TM = 64;         // output tile edge per workgroup (FP64) or wavefront (BF16)
+constexpr int kGramWaves = 4;  // FP64: wavefronts per workgroup, each with a part of the rows
+constexpr size_t kGramLds = (size_t)kGramWaves * TM * TM * sizeof(double);
 
 // Global-address-space views.  Pointers read from a job table are generic; generic loads
 // count on both the vector-memory and the LDS/scalar counters, and the compiler then
@@ -56,14 +60,162 @@ __device__ __forceinline__ void tile_pair(int p, int nt, int &ti, int &tj) {
     tj = i + rem;
 }
 
-// One 64 x 64 tile pair of one K-chunk, FP64 MFMA (one wavefront).
+// One wavefront's rows [kb, ke) of a tile of NI x NJ blocks of 16 x 16 (DIAG: a diagonal
+// tile, whose operands coincide and whose blocks below the diagonal are left out): acc is
+// left in LDS layout order, slot 4 i + j.  VEC: 16-byte aligned columns.
+template <int NI, int NJ, bool DIAG, bool VEC, int W>
+__device__ __forceinline__ void gram_rows(const double *const (&pa_)[4],
+                                          const double *const (&pb_)[4], long kb, long ke,
+                                          double *__restrict__ red, double *__restrict__ out,
+                                          int wave, int nn, int r0t, int c0t) {
+    constexpr int NB = DIAG ? 1 : NJ;  // column groups of B loaded
+    static_assert(W == 1 || W == 4, "W = 4: one value of a block per wavefront in the final sum");
+    const int lr = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4;
+    gdouble *pa[NI], *pb[NB];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) pa[i] = gptr(pa_[i]);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) pb[j] = gptr(pb_[j]);
+    v4d acc[NI][NJ];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+    auto mma_chunk = [&](const double (&a)[NI][4], const double (&b)[NB][4]) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = DIAG ? i : 0; j < NJ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                        a[i][s], DIAG ? a[j < NI ? j : 0][s] : b[j < NB ? j : 0][s], acc[i][j], 0,
+                        0, 0);
+    };
+    auto load4 = [&](gdouble *p, long r0, double (&v)[4]) {
+        if constexpr (VEC) {
+            gd2 *q = (gd2 *)(p + r0);
+            const d2 v0 = q[0], v1 = q[1];
+            v[0] = v0.x; v[1] = v0.y; v[2] = v1.x; v[3] = v1.y;
+        } else {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) v[s] = p[r0 + s];
+        }
+    };
+    auto load_chunk = [&](long k0, double (&a)[NI][4], double (&b)[NB][4]) {
+        const long r0 = k0 + 4 * lg;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) load4(pa[i], r0, a[i]);
+        if constexpr (!DIAG)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) load4(pb[j], r0, b[j]);
+    };
+    // full chunks of 16 rows, software-pipelined one chunk ahead (past the end the prefetch
+    // re-reads the final chunk); the scheduling barriers keep the prefetch ahead of the MFMAs
+    // it overlaps
+    const long len = ke > kb ? ke - kb : 0;
+    const long kend = kb + (len & ~15L);
+    if (kend > kb) {
+        double a0[NI][4], b0[NB][4], a1[NI][4], b1[NB][4];
+        const long last = kend - 16;
+        const long npairs = (kend - kb) >> 5;
+        load_chunk(kb, a0, b0);
+        for (long p = 0; p < npairs; ++p) {
+            const long k0 = kb + (p << 5);
+            load_chunk(k0 + 16, a1, b1);
+            __builtin_amdgcn_sched_barrier(0);
+            mma_chunk(a0, b0);
+            __builtin_amdgcn_sched_barrier(0);
+            load_chunk(min(k0 + 32, last), a0, b0);
+            __builtin_amdgcn_sched_barrier(0);
+            mma_chunk(a1, b1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if ((kend - kb) & 16) mma_chunk(a0, b0);
+    }
+    // tail rows [kend, ke): rows past ke are zeroed (they belong to another chunk)
+    if (kend < ke) {
+        const long r0 = kend + 4 * lg;
+        double a[NI][4], b[NB][4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const bool in = r0 + s < ke;
+            const long r = in ? r0 + s : ke - 1;
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const double x = pa[i][r];
+                a[i][s] = in ? x : 0.0;
+            }
+            if constexpr (!DIAG)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    const double y = pb[j][r];
+                    b[j][s] = in ? y : 0.0;
+                }
+        }
+        mma_chunk(a, b);
+    }
+    // FP64 16x16 accumulator layout: value v of lane l is row l/16 + 4v, column l%16
+    if constexpr (W == 1) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = DIAG ? i : 0; j < NJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int r = r0t + 16 * i + lg + 4 * v;
+                    const int c = c0t + 16 * j + lr;
+                    if (r < nn && c < nn) out[(long)c * nn + r] = acc[i][j][v];
+                }
+        return;
+    }
+    // Sum over the wavefronts: every tile into LDS, then each thread adds the same entries of
+    // the four in order.  The LDS stores go through an address the compiler cannot see to be
+    // LDS (flat stores): LDS stores, or VALU additions into acc, make it keep acc in ordinary
+    // registers and move all of it to and from the accumulation registers in every loop
+    // iteration (512 columns: 4.68 instead of 4.32 ms).
+    const int lane = threadIdx.x & 63;
+    double *dst = red + wave * (TM * TM) + lane;
+    asm("" : "+v"(dst));
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = DIAG ? i : 0; j < NJ; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) dst[64 * (16 * i + 4 * j + v)] = acc[i][j][v];
+    __syncthreads();
+    // this thread takes value v = wave of every block
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = DIAG ? i : 0; j < NJ; ++j) {
+            const double *src = red + 64 * (16 * i + 4 * j + wave) + lane;
+            double t = src[0];
+#pragma unroll
+            for (int w = 1; w < W; ++w) t += src[w * TM * TM];
+            const int r = r0t + 16 * i + lg + 4 * wave;
+            const int c = c0t + 16 * j + lr;
+            if (r < nn && c < nn) out[(long)c * nn + r] = t;
+        }
+}
+
+// One 64 x 64 tile pair of one K-chunk, FP64 MFMA, by W wavefronts.  W = 4: each takes a
+// quarter of the chunk's rows and their tiles are summed through LDS in a fixed order, so a
+// chunk costs one partial instead of one per wavefront (with one wavefront per chunk the
+// partials of 96 columns at 64^3 rows were 75 MB written and read against 201 MB of
+// operands).  W = 1 (many tile pairs): the wavefronts of a CU are different tile pairs of
+// the same rows and share them in the caches (512 columns at 96^3 rows: 4.60 ms with W = 4).  16 x 16 blocks past the last column, or below the diagonal of a diagonal
+// tile, are not computed (an FP64 MFMA occupies its matrix core for 64 cycles, and with 96
+// columns 27 of 48 blocks are of that kind): the tile's extent selects a form whose loops
+// hold its blocks alone.
 // CROSS: the n x n block X^T Y alone (tile (ti, tj) = pair / ntn, pair % ntn over X
 // columns x Y columns), partials n x n per split.
-template <bool CROSS = false>
+template <int W, bool CROSS = false>
 __device__ __forceinline__ void gram_f64_tile(const double *__restrict__ X,
                                               const double *__restrict__ Y, long ld, long ng,
                                               int n, long kchunk, double *__restrict__ part,
-                                              int vec_ok, int pair, int split) {
+                                              int vec_ok, int pair, int split,
+                                              double *__restrict__ red) {
     const int nn = CROSS ? n : 2 * n;
     const int nt = (nn + TM - 1) / TM;
     int ti, tj;
@@ -73,165 +225,127 @@ __device__ __forceinline__ void gram_f64_tile(const double *__restrict__ X,
     } else {
         tile_pair(pair, nt, ti, tj);
     }
-    const long kb = (long)split * kchunk;
-    const long ke = min(ng, kb + kchunk);
-    const int lane = threadIdx.x;
-    const int lr = lane & 15, lg = lane >> 4;
-
+    // this wavefront's rows: its part of the chunk, in whole 16-row MFMA steps (the index is
+    // made a scalar: a row count the compiler takes for divergent costs it the accumulation
+    // registers of the loop)
+    const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const long sub = ((kchunk + W - 1) / W + 15) / 16 * 16;
+    const long kend_chunk = min(ng, (long)(split + 1) * kchunk);
+    const long kb = min(kend_chunk, (long)split * kchunk + wave * sub);
+    const long ke = min(kend_chunk, kb + sub);
+    const int lr = threadIdx.x & 15;
     // Columns beyond 2n read column 0: their products only reach entries that are never
     // stored, so the loads need no guard.  (Guarded loads become branches, and the
     // compiler then waits for every load in flight before the MFMAs.)
-    gdouble *pa[4];
-    gdouble *pb[4];
+    const double *pa[4], *pb[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int ca = ti * TM + 16 * i + lr;
         const int cb = tj * TM + 16 * i + lr;
         if (CROSS) {
-            pa[i] = gptr(X + (long)(ca < nn ? ca : 0) * ld);
-            pb[i] = gptr(Y + (long)(cb < nn ? cb : 0) * ld);
+            pa[i] = X + (long)(ca < nn ? ca : 0) * ld;
+            pb[i] = Y + (long)(cb < nn ? cb : 0) * ld;
         } else {
-            pa[i] = gptr(ca < nn ? zcol(X, Y, ld, n, ca) : X);
-            pb[i] = gptr(cb < nn ? zcol(X, Y, ld, n, cb) : X);
+            pa[i] = ca < nn ? zcol(X, Y, ld, n, ca) : X;
+            pb[i] = cb < nn ? zcol(X, Y, ld, n, cb) : X;
         }
     }
-    v4d acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
-
-    auto mma_chunk = [&](const double (&a)[4][4], const double (&b)[4][4]) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][s], b[j][s], acc[i][j],
-                                                                    0, 0, 0);
-    };
-    // rows [kb, kend) in full chunks of 16, software-pipelined one chunk ahead (past the end
-    // the prefetch re-reads the final chunk); the scheduling barriers keep the prefetch
-    // ahead of the MFMAs it overlaps
-    const long len = ke > kb ? ke - kb : 0;
-    const long kend = kb + (len & ~15L);
-    auto run = [&](auto vec) {
-        auto load_chunk = [&](long k0, double (&a)[4][4], double (&b)[4][4]) {
-            const long r0 = k0 + 4 * lg;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if constexpr (decltype(vec)::value) {
-                    gd2 *qa = (gd2 *)(pa[i] + r0);
-                    gd2 *qb = (gd2 *)(pb[i] + r0);
-                    const d2 a0 = qa[0], a1 = qa[1], b0 = qb[0], b1 = qb[1];
-                    a[i][0] = a0.x; a[i][1] = a0.y; a[i][2] = a1.x; a[i][3] = a1.y;
-                    b[i][0] = b0.x; b[i][1] = b0.y; b[i][2] = b1.x; b[i][3] = b1.y;
-                } else {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        a[i][s] = pa[i][r0 + s];
-                        b[i][s] = pb[i][r0 + s];
-                    }
-                }
-            }
-        };
-        if (kend > kb) {
-            double a0[4][4], b0[4][4], a1[4][4], b1[4][4];
-            const long last = kend - 16;
-            const long npairs = (kend - kb) >> 5;
-            load_chunk(kb, a0, b0);
-            for (long p = 0; p < npairs; ++p) {
-                const long k0 = kb + (p << 5);
-                load_chunk(k0 + 16, a1, b1);
-                __builtin_amdgcn_sched_barrier(0);
-                mma_chunk(a0, b0);
-                __builtin_amdgcn_sched_barrier(0);
-                load_chunk(min(k0 + 32, last), a0, b0);
-                __builtin_amdgcn_sched_barrier(0);
-                mma_chunk(a1, b1);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if ((kend - kb) & 16) mma_chunk(a0, b0);
-        }
-    };
-    if (vec_ok) run(std::true_type{});
-    else run(std::false_type{});
-    // tail rows [kend, ke): rows past ke are zeroed (they belong to another chunk)
-    if (kend < ke) {
-        const long r0 = kend + 4 * lg;
-        double a[4][4], b[4][4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const bool in = r0 + s < ke;
-                const long r = in ? r0 + s : ke - 1;
-                const double x = pa[i][r], y = pb[i][r];
-                a[i][s] = in ? x : 0.0;
-                b[i][s] = in ? y : 0.0;
-            }
-        mma_chunk(a, b);
-    }
-    // FP64 16x16 accumulator layout: value v of lane l is row l/16 + 4v, column l%16
     double *out = part + (long)split * nn * nn;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int r = ti * TM + 16 * i + lg + 4 * v;
-                const int c = tj * TM + 16 * j + lr;
-                if (r < nn && c < nn) out[(long)c * nn + r] = acc[i][j][v];
-            }
+    const int r0 = ti * TM, c0 = tj * TM;
+    // column blocks of the tile; its row blocks are 4 off the diagonal of the symmetric
+    // Gram (only the last tile is cut), unaligned operands take the whole tile
+    const int nj = min(4, (nn - c0 + 15) / 16);
+#define QO_GRAM(NI, NJ, D, V) gram_rows<NI, NJ, D, V, W>(pa, pb, kb, ke, red, out, wave, nn, r0, c0)
+    if (!vec_ok) {
+        if (!CROSS && ti == tj) QO_GRAM(4, 4, true, false);
+        else QO_GRAM(4, 4, false, false);
+    } else if (CROSS) {
+        QO_GRAM(4, 4, false, true);
+    } else if (ti == tj) {
+        if (nj == 4) QO_GRAM(4, 4, true, true);
+        else if (nj == 3) QO_GRAM(3, 3, true, true);
+        else if (nj == 2) QO_GRAM(2, 2, true, true);
+        else QO_GRAM(1, 1, true, true);
+    } else {
+        if (nj == 4) QO_GRAM(4, 4, false, true);
+        else if (nj == 3) QO_GRAM(4, 3, false, true);
+        else if (nj == 2) QO_GRAM(4, 2, false, true);
+        else QO_GRAM(4, 1, false, true);
+    }
+#undef QO_GRAM
 }
 
-__global__ __launch_bounds__(64) void k_gram_f64(const double *__restrict__ X,
+template <int W>
+__global__ __launch_bounds__(64 * W) void k_gram_f64(const double *__restrict__ X,
                                                  const double *__restrict__ Y, long ld, long ng,
                                                  int n, long kchunk, double *__restrict__ part,
                                                  int vec_ok) {
+    extern __shared__ double red[];
     // pairs of one K-chunk on one XCD: they read the same rows of the 2n columns
     const int nt = (2 * n + TM - 1) / TM;
     const int npairs = nt * (nt + 1) / 2;
     const int L = xcd_remap(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     const int split = L / npairs;
-    gram_f64_tile(X, Y, ld, ng, n, kchunk, part, vec_ok, L - split * npairs, split);
+    gram_f64_tile<W>(X, Y, ld, ng, n, kchunk, part, vec_ok, L - split * npairs, split, red);
 }
 
-__global__ __launch_bounds__(64) void k_gram_cross_f64(const double *__restrict__ X,
+template <int W>
+__global__ __launch_bounds__(64 * W) void k_gram_cross_f64(const double *__restrict__ X,
                                                        const double *__restrict__ Y, long ld,
                                                        long ng, int n, long kchunk,
                                                        double *__restrict__ part, int vec_ok) {
+    extern __shared__ double red[];
     const int nt = (n + TM - 1) / TM;
     const int npairs = nt * nt;
     const int L = xcd_remap(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     const int split = L / npairs;
-    gram_f64_tile<true>(X, Y, ld, ng, n, kchunk, part, vec_ok, L - split * npairs, split);
+    gram_f64_tile<W, true>(X, Y, ld, ng, n, kchunk, part, vec_ok, L - split * npairs, split, red);
+}
+
+// Sum over the partials of 64 consecutive entries starting at e0: the workgroup's wavefronts
+// take every kRedWaves-th partial, their sums are added in order.  Every load of a wavefront
+// is independent and coalesced, so the pass costs a few memory round trips; one thread per
+// entry walking all partials in turn cost one per partial (1024 partials of 96 columns:
+// 110 us, 64 columns of the batch's 256^2 grids 34 us).  Complete in wavefront 0; the
+// caller separates two calls with a barrier.
+constexpr int kRedWaves = 16;
+__device__ __forceinline__ double sum_parts(const double *__restrict__ part, long total,
+                                            int nsplit, long e, double *__restrict__ sh) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double s = 0.0;
+    if (e < total) {
+#pragma unroll 8
+        for (int k = w; k < nsplit; k += kRedWaves) s += part[(long)k * total + e];
+    }
+    if (w) sh[(w - 1) * 64 + lane] = s;
+    __syncthreads();
+    if (w == 0)
+#pragma unroll
+        for (int i = 0; i < kRedWaves - 1; ++i) s += sh[i * 64 + lane];
+    return s;
 }
 
 // G = w sum_s part[s] (n x n, no mirroring)
-__global__ void k_gram_cross_reduce(const double *__restrict__ part, int n, int nsplit, double w,
-                                    double *__restrict__ G) {
+__global__ __launch_bounds__(64 * kRedWaves) void k_gram_cross_reduce(
+    const double *__restrict__ part, int n, int nsplit, double w, double *__restrict__ G) {
+    __shared__ double sh[64 * (kRedWaves - 1)];
     const long total = (long)n * n;
-    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-         e += (long)gridDim.x * blockDim.x) {
-        double s = 0.0;
-        for (int k = 0; k < nsplit; ++k) s += part[(long)k * total + e];
-        G[e] = w * s;
-    }
+    const long e = (long)blockIdx.x * 64 + (threadIdx.x & 63);
+    const double s = sum_parts(part, total, nsplit, e, sh);
+    if (threadIdx.x < 64 && e < total) G[e] = w * s;
 }
 
 // Grouped batches: job blockIdx.z, (pair, split) from blockIdx.x.
-__global__ __launch_bounds__(64) void k_gram_f64_batch(const GramJob *__restrict__ jobs, long ld,
+__global__ __launch_bounds__(64 * kGramWaves) void k_gram_f64_batch(const GramJob *__restrict__ jobs, long ld,
                                                        long ng, int vec_ok) {
+    extern __shared__ double red[];
     const GramJob J = jobs[blockIdx.z];
     const int nt = (2 * J.n + TM - 1) / TM;
     const int npairs = nt * (nt + 1) / 2;
     if ((int)blockIdx.x >= npairs * J.nsplit) return;
     const int split = blockIdx.x / npairs;
-    gram_f64_tile(J.X, J.Y, ld, ng, J.n, J.kchunk, J.part, vec_ok, blockIdx.x - split * npairs,
-                  split);
+    gram_f64_tile<kGramWaves>(J.X, J.Y, ld, ng, J.n, J.kchunk, J.part, vec_ok, blockIdx.x - split * npairs,
+                  split, red);
 }
 
 // One FP64 block (n columns, leading dimension ld) rounded to BF16 in the row-blocked
@@ -387,34 +501,38 @@ __global__ __launch_bounds__(1024) void k_gram_bf16_super(const __bf16 *__restri
             }
 }
 
-// G[r][c] = w * sum_s part[s][min(r,c)][max(r,c)]
-__global__ void k_gram_reduce(const double *__restrict__ part, int nn, int nsplit, double w,
-                              double *__restrict__ G) {
-    // each partial entry (r <= c) is read once and gives both G[r][c] and G[c][r]
+// G[r][c] = w * sum_s part[s][min(r,c)][max(r,c)], 64 entries from 64 chunk on: each entry
+// with r <= c is summed once and gives both G[r][c] and G[c][r].
+__device__ __forceinline__ void gram_reduce_chunk(const double *__restrict__ part, int nn,
+                                                  int nsplit, double w, double *__restrict__ G,
+                                                  long chunk, double *__restrict__ sh) {
     const long total = (long)nn * nn;
-    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-         e += (long)gridDim.x * blockDim.x) {
-        const int r = (int)(e % nn), c = (int)(e / nn);
-        if (r > c) continue;
-        double s = 0.0;
-        for (int k = 0; k < nsplit; ++k) s += part[(long)k * total + e];
+    const long e = chunk * 64 + (threadIdx.x & 63);
+    const int c = (int)(e / nn), r = (int)(e - (long)c * nn);
+    const bool mine = e < total && r <= c;
+    const double s = sum_parts(part, total, nsplit, mine ? e : total, sh);
+    if (threadIdx.x < 64 && mine) {
         G[e] = w * s;
         G[(long)r * nn + c] = w * s;
     }
 }
 
-__global__ void k_gram_reduce_batch(const GramJob *__restrict__ jobs, double w) {
+__global__ __launch_bounds__(64 * kRedWaves) void k_gram_reduce(const double *__restrict__ part,
+                                                                int nn, int nsplit, double w,
+                                                                double *__restrict__ G) {
+    __shared__ double sh[64 * (kRedWaves - 1)];
+    gram_reduce_chunk(part, nn, nsplit, w, G, blockIdx.x, sh);
+}
+
+__global__ __launch_bounds__(64 * kRedWaves) void k_gram_reduce_batch(
+    const GramJob *__restrict__ jobs, double w) {
+    __shared__ double sh[64 * (kRedWaves - 1)];
     const GramJob J = jobs[blockIdx.z];
     const int nn = 2 * J.n;
-    const long total = (long)nn * nn;
-    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-         e += (long)gridDim.x * blockDim.x) {
-        const int r = (int)(e % nn), c = (int)(e / nn);
-        const int a = min(r, c), b = max(r, c);
-        const long o = (long)b * nn + a;
-        double s = 0.0;
-        for (int k = 0; k < J.nsplit; ++k) s += J.part[(long)k * total + o];
-        J.G[e] = w * s;
+    const long chunks = ((long)nn * nn + 63) / 64;
+    for (long ch = blockIdx.x; ch < chunks; ch += gridDim.x) {
+        gram_reduce_chunk(J.part, nn, J.nsplit, w, J.G, ch, sh);
+        __syncthreads();  // sh is rewritten by the next chunk
     }
 }
 
@@ -423,12 +541,13 @@ __global__ void k_gram_reduce_batch(const GramJob *__restrict__ jobs, double w) 
 hipError_t launch_gram_f64_batch(const GramJob *jobs, int njobs, int max_grid, long ld, long ng,
                                  double w, hipStream_t st) {
     if (njobs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gram_f64_batch, dim3((unsigned)max_grid, 1, (unsigned)njobs), dim3(64), 0,
+    hipLaunchKernelGGL(k_gram_f64_batch, dim3((unsigned)max_grid, 1, (unsigned)njobs),
+                       dim3(64 * kGramWaves), kGramLds,
                        st, jobs, ld, ng, 1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gram_reduce_batch, dim3(64, 1, (unsigned)njobs), dim3(256), 0, st, jobs,
-                       w);
+    hipLaunchKernelGGL(k_gram_reduce_batch, dim3(128, 1, (unsigned)njobs), dim3(64 * kRedWaves), 0,
+                       st, jobs, w);
     return hipGetLastError();
 }
 
@@ -456,15 +575,28 @@ int gram_nsplit(long ng, int n) {
     return (int)ns;
 }
 
+// Wavefronts per workgroup and row chunks of an FP64 Gram of npairs tile pairs, at most
+// `most` chunks (what the partial buffer holds).  Up to kGramPairsW4 pairs (256 columns) four
+// wavefronts: the partials of one each would be a large part of the traffic; at most
+// kGramTarget workgroups, a multiple of the 256 CUs that hold one each so that the last
+// round is not nearly empty, and at least 256 rows each (four 16-row steps per wavefront).
+// More pairs: one wavefront and all the chunks, which share their operands' rows.
+constexpr int kGramPairsW4 = 10;
+constexpr long kGramTarget = 1024;
+static int gram_f64_waves(int npairs) { return npairs <= kGramPairsW4 ? kGramWaves : 1; }
+static int gram_f64_nsplit(int npairs, long ng, int most) {
+    if (gram_f64_waves(npairs) == 1) return most;
+    const long ns = std::min(kGramTarget / npairs, (ng + 255) / 256);
+    return (int)std::max(1L, std::min(ns, (long)most));
+}
+
 size_t gram_part_elems(int n, int nsplit) { return (size_t)nsplit * 4 * n * n; }
 
 static hipError_t gram_reduce(double *part, int nn, int nsplit, double w, double *G,
                               hipStream_t st) {
-    const long total = (long)nn * nn;
-    long blocks = (total + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)blocks), dim3(256), 0, st, part, nn, nsplit,
-                       w, G);
+    const long blocks = ((long)nn * nn + 63) / 64;
+    hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)blocks), dim3(64 * kRedWaves), 0, st, part, nn,
+                       nsplit, w, G);
     return hipGetLastError();
 }
 
@@ -473,12 +605,17 @@ hipError_t launch_gram_f64(const double *X, const double *Y, long ld, long ng, i
     if (n <= 0) return hipSuccess;
     const int nt = (2 * n + TM - 1) / TM;
     const int npairs = nt * (nt + 1) / 2;
+    nsplit = gram_f64_nsplit(npairs, ng, nsplit);
     long kchunk = (ng + nsplit - 1) / nsplit;
     kchunk = (kchunk + 31) / 32 * 32;
     const int vec_ok = (ld % 2 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0) &&
                        ((reinterpret_cast<uintptr_t>(Y) & 15) == 0);
-    hipLaunchKernelGGL(k_gram_f64, dim3(npairs, nsplit), dim3(64), 0, st, X, Y, ld, ng, n, kchunk,
-                       part, vec_ok);
+    if (gram_f64_waves(npairs) == 1)
+        hipLaunchKernelGGL(k_gram_f64<1>, dim3(npairs, nsplit), dim3(64), 0, st, X, Y, ld, ng, n,
+                           kchunk, part, vec_ok);
+    else
+        hipLaunchKernelGGL(k_gram_f64<kGramWaves>, dim3(npairs, nsplit), dim3(64 * kGramWaves),
+                           kGramLds, st, X, Y, ld, ng, n, kchunk, part, vec_ok);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return gram_reduce(part, 2 * n, nsplit, w, G, st);
@@ -488,19 +625,23 @@ hipError_t launch_gram_cross_f64(const double *X, const double *Y, long ld, long
                                  double w, double *part, int nsplit, double *G, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     const int nt = (n + TM - 1) / TM;
+    nsplit = gram_f64_nsplit(nt * nt, ng, nsplit);
     long kchunk = (ng + nsplit - 1) / nsplit;
     kchunk = (kchunk + 31) / 32 * 32;
     const int vec_ok = (ld % 2 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0) &&
                        ((reinterpret_cast<uintptr_t>(Y) & 15) == 0);
-    hipLaunchKernelGGL(k_gram_cross_f64, dim3(nt * nt, nsplit), dim3(64), 0, st, X, Y, ld, ng, n,
-                       kchunk, part, vec_ok);
+    if (gram_f64_waves(nt * nt) == 1)
+        hipLaunchKernelGGL(k_gram_cross_f64<1>, dim3(nt * nt, nsplit), dim3(64), 0, st, X, Y, ld, ng,
+                           n, kchunk, part, vec_ok);
+    else
+        hipLaunchKernelGGL(k_gram_cross_f64<kGramWaves>, dim3(nt * nt, nsplit),
+                           dim3(64 * kGramWaves), kGramLds, st, X, Y, ld, ng, n, kchunk, part,
+                           vec_ok);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const long total = (long)n * n;
-    long blocks = (total + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_gram_cross_reduce, dim3((unsigned)blocks), dim3(256), 0, st, part, n,
-                       nsplit, w, G);
+    const long blocks = ((long)n * n + 63) / 64;
+    hipLaunchKernelGGL(k_gram_cross_reduce, dim3((unsigned)blocks), dim3(64 * kRedWaves), 0, st,
+                       part, n, nsplit, w, G);
     return hipGetLastError();
 }
 
