@@ -1957,14 +1957,14 @@ qo_status qo_eigenpairs(qo_handle h, int mode, double *evals, double *evecs, lon
         double *S = h->G2, *K = h->G2 + (size_t)N * N2;
         // S = V diag(l) V^T ; F = V diag(l)^{-1/2}
         HIPC(h, nn_axpby(mp(h, MP_T1), N, 0.5, S, N2, 0.5, S, N2, true, 0.0, N, N, st));
-        HIPC(h, nn_jacobi(mp(h, MP_T1), N, N, ev, mp(h, MP_T2), N, nullptr, st));
+        HIPC(h, nn_jacobi(mp(h, MP_T1), N, N, ev, mp(h, MP_T2), N, h->sortwork, st));
         HIPC(h, nn_scale_cols_rsqrt(mp(h, MP_SW), mp(h, MP_T2), N, ev, N, h->dstatus, st));
         // K' = F^T sym(K) F
         HIPC(h, nn_axpby(mp(h, MP_T1), N, 0.5, K, N2, 0.5, K, N2, true, 0.0, N, N, st));
         HIPC(h, nn_gemm(mp(h, MP_T2), N, mp(h, MP_T1), N, false, mp(h, MP_SW), N, false, N, N, N, 1.0, 0.0, 0.0, st));
         HIPC(h, nn_gemm(mp(h, MP_T1), N, mp(h, MP_SW), N, true, mp(h, MP_T2), N, false, N, N, N, 1.0, 0.0, 0.0, st));
         HIPC(h, nn_axpby(mp(h, MP_T2), N, 0.5, mp(h, MP_T1), N, 0.5, mp(h, MP_T1), N, true, 0.0, N, N, st));
-        HIPC(h, nn_jacobi(mp(h, MP_T2), N, N, ev, mp(h, MP_Z), N, nullptr, st));
+        HIPC(h, nn_jacobi(mp(h, MP_T2), N, N, ev, mp(h, MP_Z), N, h->sortwork, st));
         HIPC(h, nn_sort(ev, mp(h, MP_Z), N, N, false, h->sortwork, st));
         HIPC(h, nn_eval_map(ev, ev, N, false, h->cfg.sigma, st));
         QOC(check_status(h, "Rayleigh-Ritz: <U,U> not positive definite"));
@@ -1990,7 +1990,7 @@ qo_status qo_eigenpairs(qo_handle h, int mode, double *evals, double *evecs, lon
         QOC(gram64(h, h->U, h->W2, h->ld, N, h->G2));
         double *M = h->G2 + (size_t)N * N2;
         HIPC(h, nn_axpby(mp(h, MP_T1), N, 0.5, M, N2, 0.5, M, N2, true, 0.0, N, N, st));
-        HIPC(h, nn_jacobi(mp(h, MP_T1), N, N, ev, mp(h, MP_T2), N, nullptr, st));
+        HIPC(h, nn_jacobi(mp(h, MP_T1), N, N, ev, mp(h, MP_T2), N, h->sortwork, st));
         HIPC(h, nn_eval_map(ev, ev, N, true, h->cfg.sigma, st));
         HIPC(h, nn_sort(ev, nullptr, N, N, false, h->sortwork, st));
     }

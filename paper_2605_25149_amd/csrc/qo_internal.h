@@ -366,7 +366,8 @@ hipError_t nn_gj_solve(double *A, int lda, double *B, int ldb, int n, int m, boo
                        int *status, hipStream_t st, double *work = nullptr, int *piv = nullptr);
 size_t nn_gj_work_elems(int n);
 // Symmetric eigen-decomposition by cyclic Jacobi: A (n x n, destroyed) ->
-// evals (n), V (n x n, ld n) with A = V diag V^T; unsorted.
+// evals (n), V (n x n, ld n) with A = V diag V^T; unsorted.  work: n^2 + 1 doubles.
+// Waits on the stream between sweeps when n is too large for one workgroup's LDS.
 hipError_t nn_jacobi(double *A, int lda, int n, double *evals, double *V, int ldv,
                      double *work, hipStream_t st);
 // Sort evals ascending (or descending) and permute the columns of V (may be null).

@@ -393,104 +393,208 @@ __global__ __launch_bounds__(256) void k_gjb_update(double *__restrict__ A, int 
     }
 }
 
-// Cyclic Jacobi with round-robin (circle) ordering: each round rotates n/2
-// disjoint pairs.  A <- J^T A J with J the Givens rotation zeroing A_pq.
+// Cyclic Jacobi with round-robin (circle) ordering: each round rotates n/2 disjoint pairs.
+// A <- J^T A J with J the product of the round's Givens rotations, V <- V J.  The rotations
+// of a round act on disjoint 2 x 2 blocks of A (row pair i, column pair j), so one thread
+// takes a block through both its row and its column rotation: A is read and written once
+// per round and nothing but the next round's angles waits for it.
+//
+// Rotation of pair i of round rnd (m players, m - 1 rounds; index n of an odd n is a dummy):
+// indices p < q, cosine and sine that zero A_pq.
 constexpr int JT = 1024;
 
-__global__ __launch_bounds__(JT) void k_jacobi(double *__restrict__ A, int lda, int n,
-                                               double *__restrict__ evals,
-                                               double *__restrict__ V, int ldv) {
+__device__ __forceinline__ void jac_pair(int i, int rnd, int m, int &p, int &q) {
+    if (i == 0) {
+        p = rnd % (m - 1);
+        q = m - 1;
+    } else {
+        p = (rnd + i) % (m - 1);
+        q = (rnd - i + (m - 1)) % (m - 1);
+    }
+    if (p > q) {
+        const int t = p;
+        p = q;
+        q = t;
+    }
+}
+
+__device__ __forceinline__ void jac_rot(const double *A, int lda, int n, int p, int q, double &c,
+                                        double &s) {
+    c = 1.0;
+    s = 0.0;
+    if (q >= n) return;
+    const double apq = A[(long)q * lda + p];
+    const double app = A[(long)p * lda + p];
+    const double aqq = A[(long)q * lda + q];
+    if (apq != 0.0 && fabs(apq) > 1e-300) {
+        const double th = (aqq - app) / (2.0 * apq);
+        double t;
+        if (fabs(th) > 1e150) t = 0.5 / th;
+        else t = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
+        c = 1.0 / sqrt(t * t + 1.0);
+        s = t * c;
+    }
+}
+
+// Block (rows p, q; columns r, t) of A through both rotations, from A into B (may be A).  The
+// pair's own off-diagonal entry, zero up to rounding, is stored as zero: left as rounding
+// noise, the off-diagonal mass stays near 1e-32 of the total and the iteration runs all of
+// its 60 sweeps (64 x 64) instead of the eight or nine that the quadratic convergence needs.
+__device__ __forceinline__ void jac_block(const double *A, int lda, double *B, int ldb, int n,
+                                          int p, int q, double ci, double si, int r, int t,
+                                          double cj, double sj) {
+    const bool hq = q < n, ht = t < n;  // a dummy index has no row or column
+    double pr = A[(long)r * lda + p], qr = hq ? A[(long)r * lda + q] : 0.0;
+    double pt = ht ? A[(long)t * lda + p] : 0.0, qt = hq && ht ? A[(long)t * lda + q] : 0.0;
+    const double pr1 = ci * pr - si * qr, qr1 = si * pr + ci * qr;
+    const double pt1 = ci * pt - si * qt, qt1 = si * pt + ci * qt;
+    pr = cj * pr1 - sj * pt1;
+    pt = sj * pr1 + cj * pt1;
+    qr = cj * qr1 - sj * qt1;
+    qt = sj * qr1 + cj * qt1;
+    if (p == r) pt = qr = 0.0;
+    B[(long)r * ldb + p] = pr;
+    if (hq) B[(long)r * ldb + q] = qr;
+    if (ht) B[(long)t * ldb + p] = pt;
+    if (hq && ht) B[(long)t * ldb + q] = qt;
+}
+
+__device__ double block_sum_1024(double v, double *red);
+
+// sums of squares over A: off the diagonal and all (every thread of a JT-thread block)
+__device__ __forceinline__ void jac_mass(const double *A, int lda, int n, double *red, double &off,
+                                         double &tot) {
+    off = tot = 0.0;
+    for (long e = threadIdx.x; e < (long)n * n; e += JT) {
+        const int c = (int)(e / n), r = (int)(e - (long)c * n);
+        const double v = A[(long)c * lda + r];
+        tot += v * v;
+        if (r != c) off += v * v;
+    }
+    off = block_sum_1024(off, red);
+    tot = block_sum_1024(tot, red);
+}
+
+// n <= kJacobiLds: A and V stay in one workgroup's LDS for the whole iteration (pitch odd:
+// a wavefront's consecutive rows fall in different banks).  A round is two barriers and
+// one LDS pass; with A and V in global memory (three barriers, every access an L2 round
+// trip) a 64 x 64 problem took 26.4 ms.
+constexpr int kJacobiLds = 98;
+__host__ __device__ constexpr int jac_pitch(int n) { return n | 1; }
+
+__global__ __launch_bounds__(JT) void k_jacobi_lds(const double *__restrict__ Ag, int lda, int n,
+                                                   double *__restrict__ evals,
+                                                   double *__restrict__ Vg, int ldv) {
     extern __shared__ double jsm[];
-    const int m = (n + 1) & ~1;  // even number of players; index n is a dummy
-    const int np = m / 2;
-    double *cs = jsm;            // [np] c
-    double *sn = jsm + np;       // [np] s
-    int *pp = reinterpret_cast<int *>(jsm + 2 * np);  // [np] p
-    int *qq = pp + np;                                // [np] q
     __shared__ double red[JT / 64];
-    __shared__ double off_sh, tot_sh;
+    const int m = (n + 1) & ~1;  // even number of players; index n is a dummy
+    const int np = m / 2, ld = jac_pitch(n);
+    double *A = jsm, *V = A + n * ld;
+    double *cs = V + n * ld;                          // [np] c
+    double *sn = cs + np;                             // [np] s
+    int *pp = reinterpret_cast<int *>(sn + np);       // [np] p
+    int *qq = pp + np;                                // [np] q
     const int tid = threadIdx.x;
-    for (long e = tid; e < (long)n * n; e += JT) {
-        const int r = (int)(e % n), c = (int)(e / n);
-        V[(long)c * ldv + r] = (r == c) ? 1.0 : 0.0;
+    for (int e = tid; e < n * n; e += JT) {
+        const int c = e / n, r = e - c * n;
+        A[c * ld + r] = Ag[(long)c * lda + r];
+        V[c * ld + r] = r == c ? 1.0 : 0.0;
     }
     __syncthreads();
     for (int sweep = 0; sweep < 60; ++sweep) {
-        // convergence: off-diagonal mass relative to the total
-        double off = 0.0, tot = 0.0;
-        for (long e = tid; e < (long)n * n; e += JT) {
-            const int r = (int)(e % n), c = (int)(e / n);
-            const double v = A[(long)c * lda + r];
-            tot += v * v;
-            if (r != c) off += v * v;
-        }
-        for (int o = 32; o > 0; o >>= 1) off += __shfl_xor(off, o, 64);
-        if ((tid & 63) == 0) red[tid >> 6] = off;
-        __syncthreads();
-        if (tid == 0) { double s = 0; for (int w = 0; w < JT / 64; ++w) s += red[w]; off_sh = s; }
-        __syncthreads();
-        for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o, 64);
-        if ((tid & 63) == 0) red[tid >> 6] = tot;
-        __syncthreads();
-        if (tid == 0) { double s = 0; for (int w = 0; w < JT / 64; ++w) s += red[w]; tot_sh = s; }
-        __syncthreads();
-        if (!(off_sh > 1e-32 * tot_sh)) break;
+        double off, tot;
+        jac_mass(A, ld, n, red, off, tot);
+        if (!(off > 1e-32 * tot)) break;  // the same in every thread
         for (int rnd = 0; rnd < m - 1; ++rnd) {
-            for (int i = tid; i < np; i += JT) {
+            if (tid < np) {
                 int p, q;
-                if (i == 0) {
-                    p = rnd % (m - 1);
-                    q = m - 1;
-                } else {
-                    p = (rnd + i) % (m - 1);
-                    q = (rnd - i + (m - 1)) % (m - 1);
-                }
-                if (p > q) { const int t = p; p = q; q = t; }
-                double c = 1.0, s = 0.0;
-                if (q < n) {
-                    const double apq = A[(long)q * lda + p];
-                    const double app = A[(long)p * lda + p];
-                    const double aqq = A[(long)q * lda + q];
-                    if (apq != 0.0 && fabs(apq) > 1e-300) {
-                        const double th = (aqq - app) / (2.0 * apq);
-                        double t;
-                        if (fabs(th) > 1e150) t = 0.5 / th;
-                        else t = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-                        c = 1.0 / sqrt(t * t + 1.0);
-                        s = t * c;
-                    }
-                }
-                cs[i] = c; sn[i] = s; pp[i] = p; qq[i] = q;
+                double c, s;
+                jac_pair(tid, rnd, m, p, q);
+                jac_rot(A, ld, n, p, q, c, s);
+                cs[tid] = c;
+                sn[tid] = s;
+                pp[tid] = p;
+                qq[tid] = q;
             }
             __syncthreads();
-            // rows: A <- J^T A
-            for (long e = tid; e < (long)np * n; e += JT) {
-                const int i = (int)(e / n), j = (int)(e % n);
-                const int p = pp[i], q = qq[i];
-                if (q >= n) continue;
-                const double c = cs[i], s = sn[i];
-                const double ap = A[(long)j * lda + p], aq = A[(long)j * lda + q];
-                A[(long)j * lda + p] = c * ap - s * aq;
-                A[(long)j * lda + q] = s * ap + c * aq;
+            for (int e = tid; e < np * np; e += JT) {
+                const int j = e / np, i = e - j * np;
+                jac_block(A, ld, A, ld, n, pp[i], qq[i], cs[i], sn[i], pp[j], qq[j], cs[j], sn[j]);
             }
-            __syncthreads();
-            // columns: A <- A J, V <- V J
-            for (long e = tid; e < (long)np * n; e += JT) {
-                const int i = (int)(e / n), j = (int)(e % n);
-                const int p = pp[i], q = qq[i];
+            for (int e = tid; e < np * n; e += JT) {
+                const int j = e / n, r = e - j * n;
+                const int p = pp[j], q = qq[j];
                 if (q >= n) continue;
-                const double c = cs[i], s = sn[i];
-                const double ap = A[(long)p * lda + j], aq = A[(long)q * lda + j];
-                A[(long)p * lda + j] = c * ap - s * aq;
-                A[(long)q * lda + j] = s * ap + c * aq;
-                const double vp = V[(long)p * ldv + j], vq = V[(long)q * ldv + j];
-                V[(long)p * ldv + j] = c * vp - s * vq;
-                V[(long)q * ldv + j] = s * vp + c * vq;
+                const double c = cs[j], s = sn[j];
+                const double vp = V[p * ld + r], vq = V[q * ld + r];
+                V[p * ld + r] = c * vp - s * vq;
+                V[q * ld + r] = s * vp + c * vq;
             }
             __syncthreads();
         }
     }
-    for (int i = tid; i < n; i += JT) evals[i] = A[(long)i * lda + i];
+    for (int i = tid; i < n; i += JT) evals[i] = A[i * ld + i];
+    for (int e = tid; e < n * n; e += JT) {
+        const int c = e / n, r = e - c * n;
+        Vg[(long)c * ldv + r] = V[c * ld + r];
+    }
+}
+
+// Larger n: one launch per round over the whole chip, A from one buffer to another (a block
+// needs the round's angles, which other workgroups' blocks hold).  Workgroup (bi, bj): 16 x
+// 16 blocks; z = 1: rows 32 bi .. 32 bi + 31 of V for 16 column pairs.
+constexpr int JB = 16;
+__global__ __launch_bounds__(JB * JB) void k_jacobi_round(const double *__restrict__ A, int lda,
+                                                          double *__restrict__ B, int ldb, int n,
+                                                          int rnd, double *__restrict__ V,
+                                                          int ldv) {
+    __shared__ double cs[2][JB], sn[2][JB];
+    __shared__ int pp[2][JB], qq[2][JB];
+    const int m = (n + 1) & ~1, np = m / 2;
+    const int ti = threadIdx.x & (JB - 1), tj = threadIdx.x / JB;
+    if (threadIdx.x < 2 * JB) {
+        const int side = threadIdx.x / JB;  // 0: row pairs, 1: column pairs
+        const int i = min((int)(side ? blockIdx.y : blockIdx.x) * JB + ti, np - 1);
+        int p, q;
+        double c, s;
+        jac_pair(i, rnd, m, p, q);
+        jac_rot(A, lda, n, p, q, c, s);
+        cs[side][ti] = c;
+        sn[side][ti] = s;
+        pp[side][ti] = p;
+        qq[side][ti] = q;
+    }
+    __syncthreads();
+    if ((int)blockIdx.y * JB + tj >= np) return;
+    if (blockIdx.z == 0) {
+        if ((int)blockIdx.x * JB + ti >= np) return;
+        jac_block(A, lda, B, ldb, n, pp[0][ti], qq[0][ti], cs[0][ti], sn[0][ti], pp[1][tj],
+                  qq[1][tj], cs[1][tj], sn[1][tj]);
+        return;
+    }
+    const int p = pp[1][tj], q = qq[1][tj];
+    if (q >= n) return;
+    const double c = cs[1][tj], s = sn[1][tj];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int r = (int)blockIdx.x * 2 * JB + h * JB + ti;
+        if (r >= n) continue;
+        const double vp = V[(long)p * ldv + r], vq = V[(long)q * ldv + r];
+        V[(long)p * ldv + r] = c * vp - s * vq;
+        V[(long)q * ldv + r] = s * vp + c * vq;
+    }
+}
+
+// *more = 1 while the off-diagonal mass of A is above the convergence threshold; the
+// current diagonal goes to evals
+__global__ __launch_bounds__(JT) void k_jacobi_check(const double *__restrict__ A, int lda, int n,
+                                                     int *__restrict__ more,
+                                                     double *__restrict__ evals) {
+    __shared__ double red[JT / 64];
+    double off, tot;
+    jac_mass(A, lda, n, red, off, tot);
+    if (threadIdx.x == 0) *more = off > 1e-32 * tot ? 1 : 0;
+    for (int i = threadIdx.x; i < n; i += JT) evals[i] = A[(long)i * lda + i];
 }
 
 // Rank sort (stable) of evals with the matching column permutation of V.
@@ -659,12 +763,38 @@ size_t nn_gj_work_elems(int n) { return (size_t)n * GB + GB * GB + 8; }
 
 hipError_t nn_jacobi(double *A, int lda, int n, double *evals, double *V, int ldv, double *work,
                      hipStream_t st) {
-    (void)work;
     if (n <= 0) return hipSuccess;
-    const int m = (n + 1) & ~1;
-    const size_t smem = (size_t)m / 2 * (2 * sizeof(double) + 2 * sizeof(int));
-    hipLaunchKernelGGL(k_jacobi, dim3(1), dim3(JT), smem, st, A, lda, n, evals, V, ldv);
-    return hipGetLastError();
+    const int m = (n + 1) & ~1, np = m / 2;
+    if (n <= kJacobiLds) {
+        const size_t smem = (size_t)2 * n * jac_pitch(n) * sizeof(double) +
+                            (size_t)np * (2 * sizeof(double) + 2 * sizeof(int));
+        hipLaunchKernelGGL(k_jacobi_lds, dim3(1), dim3(JT), smem, st, A, lda, n, evals, V, ldv);
+        return hipGetLastError();
+    }
+    // V = I; then sweeps of m - 1 rounds, the buffers swapped after each
+    int *more = reinterpret_cast<int *>(work + (size_t)n * n);
+    hipError_t e = nn_axpby(V, ldv, 0.0, nullptr, n, 0.0, nullptr, n, false, 1.0, n, n, st);
+    if (e != hipSuccess) return e;
+    double *buf[2] = {A, work};
+    int ld[2] = {lda, n}, cur = 0;
+    const unsigned nb = (unsigned)((np + JB - 1) / JB);
+    for (int sweep = 0;; ++sweep) {
+        hipLaunchKernelGGL(k_jacobi_check, dim3(1), dim3(JT), 0, st, buf[cur], ld[cur], n, more,
+                           evals);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if (sweep == 60) return hipSuccess;
+        int h = 0;
+        if ((e = hipMemcpyAsync(&h, more, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess)
+            return e;
+        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+        if (!h) return hipSuccess;
+        for (int rnd = 0; rnd < m - 1; ++rnd) {
+            hipLaunchKernelGGL(k_jacobi_round, dim3(nb, nb, 2), dim3(JB * JB), 0, st, buf[cur],
+                               ld[cur], buf[cur ^ 1], ld[cur ^ 1], n, rnd, V, ldv);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            cur ^= 1;
+        }
+    }
 }
 
 hipError_t nn_sort(double *evals, double *V, int ldv, int n, bool descending, double *work,

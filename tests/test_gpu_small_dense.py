@@ -1,7 +1,10 @@
-"""FP64 Gram matrices at the edges of their tilings, against NumPy on the same data.
+"""FP64 Gram matrices and the device eigensolver at the edges of their tilings, against
+NumPy / SciPy on the same data.
 
-Tolerance: a Gram entry is a sum of ng products; split sums round it to about sqrt(ng) eps
-relative to the diagonal, far below 1e-13 for these sizes.
+Tolerances: a Gram entry is a sum of ng products; split sums round it to about
+sqrt(ng) eps relative to the diagonal, far below 1e-13 for these sizes.  The Jacobi
+iteration is backward stable: eigenvalues within a modest multiple of n eps cond(S) of
+max |lambda| (n <= 131, cond(S) < 20 here), bounded by 1e-11.
 """
 import numpy as np
 import pytest
@@ -37,3 +40,27 @@ def test_gram_edges(ncols, ng):
         g = G.cpu().numpy().reshape(2 * ncols, 2 * ncols)
         assert np.max(np.abs(g - ref)) <= 1e-13 * np.max(np.abs(ref))
         assert np.array_equal(g, g.T)
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 16, 33, 97, 98, 99, 100, 131])
+def test_eigenpairs_sizes(N):
+    import scipy.linalg
+
+    torch, B = _mods()
+    n = (12, 10, 11)
+    ng = n[0] * n[1] * n[2]
+    rng = np.random.default_rng(N)
+    with B.Solver(3, n, N, sigma=0.25) as s:
+        s.set_potential(5.0 * rng.standard_normal(ng) + 40.0)
+        s.set_state(rng.standard_normal((ng, N)))
+        S, K = s.gram()
+        lam, vec = s.eigenpairs("ritz", vectors=True)
+        ref = scipy.linalg.eigh(0.5 * (K + K.T), S, eigvals_only=True) - 0.25
+        assert np.max(np.abs(lam - ref)) <= 1e-11 * np.max(np.abs(ref))
+        assert np.all(np.diff(lam) >= 0.0)
+        HV = s.apply(vec)
+        w = 1.0 / np.prod([m + 1.0 for m in n])
+        V = vec.cpu().numpy()
+        T = w * (V @ HV.cpu().numpy().T)
+        assert np.max(np.abs(w * (V @ V.T) - np.eye(N))) <= 1e-11
+        assert np.max(np.abs(T - np.diag(ref + 0.25))) <= 1e-11 * np.max(np.abs(ref))
