@@ -88,6 +88,8 @@ struct qo_ctx {
     int *need = nullptr, *nneed = nullptr;
     double rel_delta = 0.1;
     bool rel = true;
+    bool colpcg = false;  // FP64 Jacobi solves take one workgroup per column
+    int colchunk = 8192;  // iterations per launch of that form
     // fast-Poisson preconditioner (precond == 1)
     bool dst = false;
     DstPlan dp{};
@@ -438,6 +440,47 @@ qo_status precondition_p(qo_ctx *c, const float *R, const float *Pold, float *Pn
     return QO_OK;
 }
 
+// FP64 Jacobi-PCG with a workgroup per column (launch_pcg_column): one launch for the whole
+// solve, continued every colchunk iterations so that no launch runs unboundedly long when
+// pcg_maxit is large.  Counts and states are written straight to pinned host memory.
+qo_status pcg_column(qo_ctx *c, const double *B, double *X, int ncols, int use_x0, double tol,
+                     int *its_out, const char *what) {
+    hipStream_t st = c->st;
+    int *its = poll_slot(c, 0), *state = poll_slot(c, 1);
+    const int maxit = c->cfg.pcg_maxit;
+    int running = 0;
+    for (int k0 = 0;;) {
+        const int kend = maxit - k0 > c->colchunk ? k0 + c->colchunk : maxit;
+        hipEvent_t e = prof_begin(c);
+        HIPC(c, launch_pcg_column(c->g, c->vs, c->dinv, B, X, c->r, c->pa, c->ld, ncols, use_x0, tol,
+                                  k0, kend, kend == maxit, c->part, its, state, st));
+        prof_end(c, QO_KERNEL_CG_F64, e);
+        HIPC(c, hipStreamSynchronize(st));
+        prof_harvest(c);
+        running = 0;
+        int code = 0, col = 0;
+        for (int j = 0; j < ncols; ++j) {
+            running += state[j] == kColRunning ? 1 : 0;
+            if (state[j] == kColRunning || state[j] == kColDone) continue;
+            if (!code) col = j;
+            code = std::max(code, state[j]);
+        }
+        if (code) return check_poll_err(c, code, col, what);
+        if (running == 0 || kend == maxit) break;
+        k0 = kend;
+    }
+    if (running)
+        return fail(c, QO_ERR_PCG_NOCONV, "%s: %d of %d columns not converged after %d "
+                    "PCG iterations (tol %.3g)", what, running, ncols, maxit, tol);
+    double colits = 0.0;
+    for (int j = 0; j < ncols; ++j) {
+        its_out[j] = its[j];
+        colits += its[j];
+    }
+    if (c->prof) c->pdata.work[QO_KERNEL_CG_F64] += colits;
+    return QO_OK;
+}
+
 // PCG on all columns of B (ld c->ld) into X, precision T: Jacobi, or the
 // fast-Poisson preconditioner when c->dst.
 //
@@ -464,6 +507,8 @@ qo_status pcg(qo_ctx *c, const T *vs, const T *dinv, const T *B, T *X, T *R, T *
               int *its_out, const char *what, bool skip_init = false,
               const RoundPoll *outer = nullptr, bool *outer_done = nullptr,
               int *its_async = nullptr) {
+    if constexpr (sizeof(T) == 8)
+        if (c->colpcg) return pcg_column(c, B, X, ncols, use_x0, tol, its_out, what);
     const Grid &g = c->g;
     hipStream_t st = c->st;
     PcgState s = c->ps;
@@ -1629,6 +1674,10 @@ qo_status qo_create(const qo_config *cfg, void *hip_stream, qo_handle *out) {
     A(&h->nneed, 1);
     h->rel = env_int("QO_MIXED_RESTART", 0) == 0;
     if (const char *d = getenv("QO_REL_DELTA")) h->rel_delta = atof(d);
+    // a forced tiling asks for the streaming sweeps
+    h->colpcg = !h->mixed && c.precond == 0 && pcg_column_fits(h->g) && !getenv("QO_TY") &&
+                !getenv("QO_ZC");
+    h->colchunk = std::max(1, env_int("QO_COL_CHUNK", h->colchunk));
     A(&h->nact, 1);
     A(&h->dstatus, 1);
     if (c.precond == 1) {

@@ -1,5 +1,5 @@
 // Device helpers shared by the stencil-family kernels: deterministic block
-// reductions (wavefront shuffles, then a fixed-order sum over the waves), the
+// reductions (wavefront shuffles or DPP moves, then a fixed-order sum over the waves), the
 // per-column reduction of partial sums, and the FP64 -> BF16 rounding of the
 // mixed-precision Gram operands.
 #pragma once
@@ -40,6 +40,54 @@ __device__ __forceinline__ double col_sum(const double *__restrict__ part, int c
     for (int t = threadIdx.x; t < tiles; t += kThreads) s[0] += part[(long)c * tiles + t];
     block_sums<1>(s, red);
     return s[0];
+}
+
+// Sum of v over the 64 lanes of a wavefront, complete in lane 63, by DPP moves (no LDS
+// traffic, no address registers): pairs and quads by quad permutations, rows of 16 by
+// row shifts, then the row sums carried up by the row broadcasts of 15 and 31.  A lane
+// a move has no source for adds 0.
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ float dpp_move(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
+                                                                 CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ float wave_sum_lane63(float v) {
+    v += dpp_move<0xb1>(v);          // quad_perm [1,0,3,2]
+    v += dpp_move<0x4e>(v);          // quad_perm [2,3,0,1]
+    v += dpp_move<0x114>(v);         // row_shr:4
+    v += dpp_move<0x118>(v);         // row_shr:8
+    v += dpp_move<0x142, 0xa>(v);    // row_bcast:15 into rows 1 and 3
+    v += dpp_move<0x143, 0xc>(v);    // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ double dpp_move_d(double v) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double wave_sum_lane63(double v) {
+    v += dpp_move_d<0xb1>(v);
+    v += dpp_move_d<0x4e>(v);
+    v += dpp_move_d<0x114>(v);
+    v += dpp_move_d<0x118>(v);
+    v += dpp_move_d<0x142, 0xa>(v);
+    v += dpp_move_d<0x143, 0xc>(v);
+    return v;
+}
+
+// Sum of lanes 0..15, in every lane (the other lanes' values do not count).
+__device__ __forceinline__ double row_sum16(double v) {
+    v += dpp_move_d<0xb1>(v);
+    v += dpp_move_d<0x4e>(v);
+    v += dpp_move_d<0x114>(v);
+    v += dpp_move_d<0x118>(v);
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)b, 15);
+    const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), 15);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
 // Round an FP64 value to bfloat16, nearest-even on the 45 dropped mantissa bits (one

@@ -77,6 +77,8 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxWaves = 16;
 
+using dev::wave_sum_lane63;
+
 // Deterministic sum over the block (any multiple of 64 threads up to 1024).
 __device__ __forceinline__ double block_sum(double v, double *red) {
 #pragma unroll
@@ -88,42 +90,6 @@ __device__ __forceinline__ double block_sum(double v, double *red) {
     double s = 0.0;
     for (int w = 0; w < nw; ++w) s += red[w];
     return s;
-}
-
-// Sum of v over the 64 lanes of a wavefront, complete in lane 63, by DPP moves (no LDS
-// traffic, no address registers): pairs and quads by quad permutations, rows of 16 by
-// row shifts, then the row sums carried up by the row broadcasts of 15 and 31.  A lane
-// a move has no source for adds 0.
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ float dpp_move(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
-                                                                 CTRL, ROWS, 0xf, false));
-}
-__device__ __forceinline__ float wave_sum_lane63(float v) {
-    v += dpp_move<0xb1>(v);          // quad_perm [1,0,3,2]
-    v += dpp_move<0x4e>(v);          // quad_perm [2,3,0,1]
-    v += dpp_move<0x114>(v);         // row_shr:4
-    v += dpp_move<0x118>(v);         // row_shr:8
-    v += dpp_move<0x142, 0xa>(v);    // row_bcast:15 into rows 1 and 3
-    v += dpp_move<0x143, 0xc>(v);    // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ double dpp_move_d(double v) {
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xf, false);
-    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-__device__ __forceinline__ double wave_sum_lane63(double v) {
-    v += dpp_move_d<0xb1>(v);
-    v += dpp_move_d<0x4e>(v);
-    v += dpp_move_d<0x114>(v);
-    v += dpp_move_d<0x118>(v);
-    v += dpp_move_d<0x142, 0xa>(v);
-    v += dpp_move_d<0x143, 0xc>(v);
-    return v;
 }
 
 __device__ __forceinline__ v8h lds8(const _Float16 *p) {

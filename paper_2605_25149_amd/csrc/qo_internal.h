@@ -198,6 +198,19 @@ hipError_t launch_pcg_sweep2(const Grid &g, const T *vs, const T *dinv, const T 
                              long ld, int ncols, int k, PcgState s, hipStream_t st,
                              bool jac = true, bool xzero = false);
 
+// ---- a column per workgroup (qo_colpcg.hip): FP64 Jacobi-PCG of small grids ----
+// Iterations k0 .. kend of X = G B for ncols columns in one launch.  R, P (blocks) and scal
+// (4 ncols doubles) carry the columns still running from a launch to the next one from its
+// kend; last: there is none.  its[c] and state[c] (device-accessible) receive the iteration
+// count and kColRunning (kend reached), kColDone, or a qo_status code (5, 7).
+constexpr long kColPcgMax = 16384;  // points: 1024 threads x 16
+constexpr int kColRunning = 0, kColDone = 1;
+bool pcg_column_fits(const Grid &g);
+hipError_t launch_pcg_column(const Grid &g, const double *vs, const double *dinv, const double *B,
+                             double *X, double *R, double *P, long ld, int ncols, int use_x0,
+                             double tol, int k0, int kend, bool last, double *scal, int *its,
+                             int *state, hipStream_t st);
+
 // One-reduction (Chronopoulos-Gear) PCG: delta0 = u.Hu with u = D r0 into
 // part[3] (after launch_pcg_init on the same grid), then one sweep per iteration.
 template <typename T>
