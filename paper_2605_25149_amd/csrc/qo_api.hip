@@ -276,7 +276,7 @@ qo_status fail(qo_ctx *c, qo_status s, const char *fmt, ...) {
 template <typename T>
 qo_status dalloc(qo_ctx *c, T **p, size_t n) {
     void *q = nullptr;
-    if (n == 0) n = 1;
+    n += kSlack;
     hipError_t e = hipMalloc(&q, n * sizeof(T));
     if (e != hipSuccess)
         return fail(c, QO_ERR_ALLOC, "hipMalloc(%zu bytes) failed: %s", n * sizeof(T),

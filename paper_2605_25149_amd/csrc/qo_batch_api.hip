@@ -129,7 +129,7 @@ qo_status bfail(qo_batch_ctx *b, qo_status s, const char *fmt, ...) {
 template <typename T>
 qo_status balloc(qo_batch_ctx *b, T **p, size_t n) {
     void *q = nullptr;
-    if (n == 0) n = 1;
+    n += kSlack;
     if (hipMalloc(&q, n * sizeof(T)) != hipSuccess)
         return bfail(b, QO_ERR_ALLOC, "hipMalloc(%zu bytes) failed", n * sizeof(T));
     b->allocs.push_back(q);

@@ -38,6 +38,10 @@
 // match those of the product with z.  The inverse pass then never reads r.
 // "Plane" is one z-plane in 3-D and a batch of rows in 2-D; the slowest axis
 // is z in 3-D and y in 2-D.
+//
+// Rows that are not whole 16-byte groups (nx not a multiple of 8) are read and written with
+// the same wide accesses, at the element's alignment (element by element, 61 x 75 x 52 took
+// 10.9 / 13.0 / 14.6 us for the three passes instead of 7.2 / 7.9 / 9.1, 37 columns).
 #include "qo_internal.h"
 #include "qo_device.h"
 
@@ -57,6 +61,10 @@ typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v2d __attribute__((ext_vector_type(2)));
+// rows of the caller's grids start at any element: vectors with the element's alignment
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+typedef double v2du __attribute__((ext_vector_type(2), aligned(8)));
+typedef _Float16 v8hu __attribute__((ext_vector_type(8), aligned(2)));
 
 #ifndef QO_DST_NT
 #define QO_DST_NT 1
@@ -73,9 +81,9 @@ __device__ __forceinline__ void st_out(V *p, const V &v) {
 #endif
 }
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxWaves = 16;
+constexpr int kRowSlab = 32;  // rows per workgroup of the 2-D row pass
 
 using dev::wave_sum_lane63;
 
@@ -103,14 +111,6 @@ __device__ __forceinline__ void st4h(_Float16 *p, v4f a, float f) {
     h[2] = (_Float16)(a[2] * f);
     h[3] = (_Float16)(a[3] * f);
     *reinterpret_cast<v4h *>(p) = h;
-}
-
-__device__ __forceinline__ float mu_inplane(const DstPlan &p, int m) {
-    if (p.dim == 3) {
-        const int y = m / p.nx;
-        return p.mux[m - y * p.nx] + p.muy[y];
-    }
-    return p.mux[m];
 }
 
 // S_n in FP16, zero-padded to NP x NP (row-major).
@@ -196,14 +196,73 @@ __host__ __device__ inline size_t dst_plane_xt_bytes(const DstPlan &p) {
     return (b + 15) & ~(size_t)15;
 }
 
+// Four values from src on (element-aligned) ...
+__device__ __forceinline__ void load4(const float *src, float (&v)[4]) {
+    const v4fu a = *reinterpret_cast<const v4fu *>(src);
+    v[0] = a[0]; v[1] = a[1]; v[2] = a[2]; v[3] = a[3];
+}
+__device__ __forceinline__ void load4(const double *src, double (&v)[4]) {
+    const v2du a = reinterpret_cast<const v2du *>(src)[0], b = reinterpret_cast<const v2du *>(src)[1];
+    v[0] = a[0]; v[1] = a[1]; v[2] = b[0]; v[3] = b[1];
+}
+// ... and the first min(4, left) of v to dst (ALL: left >= 4).
+template <bool ALL>
+__device__ __forceinline__ void store4(float *dst, v4f v, int left) {
+    if (ALL || left >= 4) {
+        st_out(reinterpret_cast<v4fu *>(dst), (v4fu)v);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (i < left) dst[i] = v[i];
+    }
+}
+
+// sum of (v - vb) z^2 over a group of four; z is 0 past the row's end
+template <bool ALL>
+__device__ __forceinline__ double wz4(const float (&v)[4], float vb, float4 z) {
+    const float w[4] = {v[0] - vb, v[1] - vb, v[2] - vb, v[3] - vb};
+    if constexpr (ALL)
+        return (double)(w[0] * z.x * z.x + w[1] * z.y * z.y) +
+               (double)(w[2] * z.z * z.z + w[3] * z.w * z.w);
+    return (double)(w[0] * z.x * z.x) + (double)(w[1] * z.y * z.y) + (double)(w[2] * z.z * z.z) +
+           (double)(w[3] * z.w * z.w);
+}
+
+// Eight FP16 values at src, zeros from `left` on; ALL: whole 16-byte groups, aligned.
+template <bool ALL>
+__device__ __forceinline__ v8h load8(const _Float16 *src, int left) {
+    if constexpr (ALL) return *reinterpret_cast<const v8h *>(src);
+    const v8hu a = *reinterpret_cast<const v8hu *>(src);
+    v8h h;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) h[i] = i < left ? a[i] : (_Float16)0.f;
+    return h;
+}
+// The first min(8, left) of eight values in LDS to dst.
+template <bool ALL>
+__device__ __forceinline__ void store8(_Float16 *dst, const _Float16 *src, int left) {
+    const v8h h = *reinterpret_cast<const v8h *>(src);
+    if constexpr (ALL) {
+        st_out(reinterpret_cast<v8h *>(dst), h);
+    } else if (left >= 8) {
+        st_out(reinterpret_cast<v8hu *>(dst), (v8hu)h);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 7; ++i)
+            if (i < left) dst[i] = h[i];
+    }
+}
+
 // ---------------------------------------------------------------- plane pass
 //
-// Workgroup = one slab of one column: RP = 16 * waves padded rows of NXP
+// 3-D.  Workgroup = one z-plane of one column: RP = 16 * waves padded rows of NXP
 // padded x-points in LDS (FP16).  Wave w owns output rows [16w, 16w + 16).
 //   GEMM1  T = X S_x     (A = X rows from LDS, B = rows of S_x: S symmetric)
-//   GEMM2  Y = S_y T     (3-D only; T staged transposed in LDS)
+//   GEMM2  Y = S_y T     (T staged transposed in LDS)
 // Forward: X = sc * r, output FP16.  Inverse: X = t2, output z = Y / (sc lmin) in FP32.
-// VEC: rows are whole 16-byte groups (nx % 8 == 0): vector loads and stores throughout.
+// VEC: rows are whole 16-byte groups (nx % 8 == 0).  Otherwise the last group of a row is
+// loaded past the row's end (every array has some values of slack after its last one) and
+// masked, and stored value by value.
 // FP32 3-D planes (NT <= 8) are held to 80 registers: 6 waves per SIMD, four 6-wave
 // workgroups per CU, as many as their LDS allows.
 // BIG (3-D planes of more than 128 padded rows, up to 256): up to 16 waves per workgroup,
@@ -242,9 +301,8 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
 #endif
     const int TP = p.NYP + 8;
 
-    const int row0 = slab * p.rows;
-    const int rows = min(p.rows, (p.dim == 3 ? p.ny : p.ny - row0));
-    const long base = (long)col * ld + (p.dim == 3 ? (long)slab * nx * p.ny : (long)row0 * nx);
+    const int rows = p.ny;
+    const long base = (long)col * ld + (long)slab * nx * p.ny;
     const int tid = threadIdx.x, nthr = blockDim.x;
 
     // ---- stage the slab into LDS as FP16 (zero padding).  With nthr = 4 RP threads each
@@ -274,58 +332,22 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
     v8h hv[INV ? QI : 1];
     bool okq[INV ? QI : QF];
     if constexpr (!INV) {
-        if constexpr (VEC) {
 #pragma unroll
-            for (int q = 0; q < QF; ++q) {
-                const int it = tid + q * nthr;
-                const int r = it / (NXP / 4);
-                const int x = (it - r * (NXP / 4)) * 4;
-                okq[q] = r < rows && x < nx;
-                const T *src = R + (okq[q] ? base + (long)r * nx + x : base);
-                if constexpr (sizeof(T) == 4) {
-                    const float4 v = *reinterpret_cast<const float4 *>(src);
-                    rv[q][0] = v.x; rv[q][1] = v.y; rv[q][2] = v.z; rv[q][3] = v.w;
-                } else {
-                    const double2 v0 = *reinterpret_cast<const double2 *>(src);
-                    const double2 v1 = *reinterpret_cast<const double2 *>(src + 2);
-                    rv[q][0] = v0.x; rv[q][1] = v0.y; rv[q][2] = v1.x; rv[q][3] = v1.y;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < QF; ++q) {
-                const int it = tid + q * nthr;
-                const int r = it / (NXP / 4);
-                const int x = (it - r * (NXP / 4)) * 4;
-                okq[q] = r < rows && x < nx;
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    rv[q][i] = (okq[q] && x + i < nx) ? R[base + (long)r * nx + x + i] : T(0);
-            }
+        for (int q = 0; q < QF; ++q) {
+            const int it = tid + q * nthr;
+            const int r = it / (NXP / 4);
+            const int x = (it - r * (NXP / 4)) * 4;
+            okq[q] = r < rows && x < nx;
+            load4(R + (okq[q] ? base + (long)r * nx + x : base), rv[q]);
         }
     } else {
-        if constexpr (VEC) {
 #pragma unroll
-            for (int q = 0; q < QI; ++q) {
-                const int it = tid + q * nthr;
-                const int r = it / (NXP / 8);
-                const int x = (it - r * (NXP / 8)) * 8;
-                okq[q] = r < rows && x < nx;
-                hv[q] = *reinterpret_cast<const v8h *>(
-                    Hin + (okq[q] ? base + (long)r * nx + x : base));
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < QI; ++q) {
-                const int it = tid + q * nthr;
-                const int r = it / (NXP / 8);
-                const int x = (it - r * (NXP / 8)) * 8;
-                okq[q] = r < rows && x < nx;
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    hv[q][i] = (okq[q] && x + i < nx) ? Hin[base + (long)r * nx + x + i]
-                                                      : (_Float16)0.f;
-            }
+        for (int q = 0; q < QI; ++q) {
+            const int it = tid + q * nthr;
+            const int r = it / (NXP / 8);
+            const int x = (it - r * (NXP / 8)) * 8;
+            okq[q] = r < rows && x < nx;
+            hv[q] = load8<VEC>(Hin + (okq[q] ? base + (long)r * nx + x : base), nx - x);
         }
     }
     const _Float16 *SxL = nullptr;
@@ -355,7 +377,8 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
             v4h h;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                h[i] = okq[q] ? (_Float16)((float)rv[q][i] * sc) : (_Float16)0.f;
+                h[i] = okq[q] && (VEC || x + i < nx) ? (_Float16)((float)rv[q][i] * sc)
+                                                     : (_Float16)0.f;
             *reinterpret_cast<v4h *>(X + r * XP + x) = h;
         }
     } else {
@@ -378,12 +401,10 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
     // loaded now so that their latency overlaps the x-transform
     constexpr int KYM = BIG ? 8 : 4;
     v8h ay[KYM];
-    if (p.dim == 3) {
 #pragma unroll
-        for (int ks = 0; ks < KYM; ++ks)
-            ay[ks] = *reinterpret_cast<const v8h *>(
-                p.Sy + (16 * w + lr) * p.NYP + 32 * min(ks, p.NYP / 32 - 1) + 8 * lg);
-    }
+    for (int ks = 0; ks < KYM; ++ks)
+        ay[ks] = *reinterpret_cast<const v8h *>(
+            p.Sy + (16 * w + lr) * p.NYP + 32 * min(ks, p.NYP / 32 - 1) + 8 * lg);
     v4f acc[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -398,7 +419,7 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
         }
     }
 
-    if (p.dim == 3) {
+    {
         // T^T into LDS, then Y = S_y T
 #if QO_PLANE_ALIAS
         __syncthreads();
@@ -432,20 +453,11 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
                 ST[(16 * w + 4 * lg + v) * XP + 16 * j + lr] = (_Float16)acc[j][v];
         __syncthreads();
         const int g8 = NXP / 8;
-        constexpr bool vec = VEC;
         for (int it = tid; it < rows * g8; it += nthr) {
             const int r = it / g8;
             const int x = (it - r * g8) * 8;
             if (x >= nx) continue;
-            _Float16 *dst = Hout + base + (long)r * nx + x;
-            const _Float16 *src = ST + r * XP + x;
-            if constexpr (vec) {
-                st_out(reinterpret_cast<v8h *>(dst), *reinterpret_cast<const v8h *>(src));
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (x + i < nx) dst[i] = src[i];
-            }
+            store8<VEC>(Hout + base + (long)r * nx + x, ST + r * XP + x, nx - x);
         }
     } else {
         const int FP = NXP + 4;
@@ -476,63 +488,216 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
             }
             __syncthreads();
             const int hrows = min(rows - r0, RH);
-            if constexpr (PF && VEC) {
+            if constexpr (PF) {
                 // each thread owns at most QH groups of 4 (RH * NXP / 4 <= QH * nthr): the
                 // P_old and V + sigma loads are issued together (clamped into the slab),
-                // then P is stored and w z^2 summed
+                // then P is stored and w z^2 summed (z is 0 past nx)
                 constexpr int QH = QF / NH;
-                float4 po[QH], v4[QH];
+                float po[QH][4], v4[QH][4];
 #pragma unroll
                 for (int q = 0; q < QH; ++q) {
                     const int it = tid + q * nthr;
                     const int rl = it / g4, x = (it - rl * g4) * 4;
                     const bool ok = rl < hrows && x < nx;
                     const long off = ok ? (long)(r0 + rl) * nx + x : 0;
-                    po[q] = first ? float4{0.f, 0.f, 0.f, 0.f}
-                                  : *reinterpret_cast<const float4 *>(Pold + base + off);
-                    v4[q] = *reinterpret_cast<const float4 *>(vs + pbase + off);
+                    if (first) po[q][0] = po[q][1] = po[q][2] = po[q][3] = 0.f;
+                    else load4(Pold + base + off, po[q]);
+                    load4(vs + pbase + off, v4[q]);
                 }
 #pragma unroll
                 for (int q = 0; q < QH; ++q) {
                     const int it = tid + q * nthr;
                     const int rl = it / g4, x = (it - rl * g4) * 4;
                     if (rl >= hrows || x >= nx) continue;
-                    const long i0 = base + (long)(r0 + rl) * nx + x;
                     const float4 z4 = *reinterpret_cast<const float4 *>(SF + rl * FP + x);
                     const v4f pv = first ? v4f{z4.x, z4.y, z4.z, z4.w}
-                                         : v4f{z4.x + b * po[q].x, z4.y + b * po[q].y,
-                                               z4.z + b * po[q].z, z4.w + b * po[q].w};
-                    st_out(reinterpret_cast<v4f *>(Z + i0), pv);
-                    wz += (double)((v4[q].x - vb) * z4.x * z4.x + (v4[q].y - vb) * z4.y * z4.y) +
-                          (double)((v4[q].z - vb) * z4.z * z4.z + (v4[q].w - vb) * z4.w * z4.w);
+                                         : v4f{z4.x + b * po[q][0], z4.y + b * po[q][1],
+                                               z4.z + b * po[q][2], z4.w + b * po[q][3]};
+                    store4<VEC>(Z + base + (long)(r0 + rl) * nx + x, pv, nx - x);
+                    wz += wz4<VEC>(v4[q], vb, z4);
                 }
             } else {
                 for (int it = tid; it < hrows * g4; it += nthr) {
                     const int rl = it / g4;
                     const int x = (it - rl * g4) * 4;
                     if (x >= nx) continue;
-                    const long i0 = base + (long)(r0 + rl) * nx + x;
-                    const float *src = SF + rl * FP + x;
-                    if constexpr (VEC) {
-                        const float4 z4 = *reinterpret_cast<const float4 *>(src);
-                        st_out(reinterpret_cast<v4f *>(Z + i0), v4f{z4.x, z4.y, z4.z, z4.w});
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            if (x + i >= nx) break;
-                            Z[i0 + i] = first ? src[i] : src[i] + b * Pold[i0 + i];
-                            if constexpr (PF) {
-                                const float wv = vs[pbase + (long)(r0 + rl) * nx + x + i] - vb;
-                                wz += (double)(wv * src[i] * src[i]);
-                            }
-                        }
-                    }
+                    const float4 z4 = *reinterpret_cast<const float4 *>(SF + rl * FP + x);
+                    store4<VEC>(Z + base + (long)(r0 + rl) * nx + x, v4f{z4.x, z4.y, z4.z, z4.w},
+                                nx - x);
                 }
             }
         }
         if constexpr (PF) {
             wz = wave_sum_lane63(wz);
             if ((tid & 63) == 63) wzp[((long)col * p.nslab + slab) * (nthr >> 6) + (tid >> 6)] = wz;
+        }
+    }
+}
+
+// ---------------------------------------------------------------- row pass
+//
+// The plane pass of 2-D grids: T = X S_x alone.  Workgroup = 32 rows of one column, four
+// waves; wave w owns the 16-point column tiles w, w + 4, ... of both 16-row blocks and reads
+// its part of S_x straight into registers, all of it at once and together with the rows.
+// 2-D blocks are small (199 x 199 x 15: 1.2 MB of FP16), so the pass is a chain of memory
+// round trips: here the scale, then rows and S_x, then the stores.  With 64 rows per
+// workgroup and every wave reading all of S_x step by step (above 128 points through L2) that
+// grid had 60 workgroups and took 23.4 / 16.6 us (forward / inverse).
+template <typename T, bool INV, int NT, bool VEC, bool PF>
+__global__ __launch_bounds__(256) void k_dst_rows(DstPlan p, const T *__restrict__ R,
+                                                  const _Float16 *__restrict__ Hin,
+                                                  _Float16 *__restrict__ Hout,
+                                                  float *__restrict__ Z, long ld,
+                                                  const float *__restrict__ pcs,
+                                                  const float *__restrict__ Pold = nullptr,
+                                                  const float *__restrict__ beta = nullptr,
+                                                  const float *__restrict__ vs = nullptr,
+                                                  double *__restrict__ wzp = nullptr) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int NXP = 16 * NT, XP = NXP + 8, KX = NT / 2, NJ = (NT + 3) / 4;
+    const int L = xcd_remap(blockIdx.x, gridDim.x);
+    int col, slab;
+    plane_slab_of(L, p.nslab, col, slab);
+    const float sc = pcs[col];
+    if (sc == 0.f) return;  // column converged or inactive (uniform over the block)
+    const int nx = p.nx, row0 = slab * kRowSlab;
+    const int rows = min(kRowSlab, p.ny - row0);
+    const long base = (long)col * ld + (long)row0 * nx;
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+    _Float16 *X = reinterpret_cast<_Float16 *>(smem);
+
+    v8h sx[KX][NJ];
+#pragma unroll
+    for (int ks = 0; ks < KX; ++ks)
+#pragma unroll
+        for (int t = 0; t < NJ; ++t)
+            sx[ks][t] = *reinterpret_cast<const v8h *>(
+                p.Sx + (16 * min(w + 4 * t, NT - 1) + lr) * NXP + 32 * ks + 8 * lg);
+    if constexpr (!INV) {
+        constexpr int QF = NT / 2;  // groups of 4 per thread
+        T rv[QF][4];
+        bool ok[QF];
+#pragma unroll
+        for (int q = 0; q < QF; ++q) {
+            const int it = tid + q * 256, r = it / (NXP / 4), x = (it - r * (NXP / 4)) * 4;
+            ok[q] = r < rows && x < nx;
+            load4(R + (ok[q] ? base + (long)r * nx + x : base), rv[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < QF; ++q) {
+            const int it = tid + q * 256, r = it / (NXP / 4), x = (it - r * (NXP / 4)) * 4;
+            v4h h;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                h[i] = ok[q] && (VEC || x + i < nx) ? (_Float16)((float)rv[q][i] * sc)
+                                                    : (_Float16)0.f;
+            *reinterpret_cast<v4h *>(X + r * XP + x) = h;
+        }
+    } else {
+        constexpr int QI = (NT + 3) / 4;  // groups of 8 per thread
+        v8h hv[QI];
+        bool ok[QI];
+#pragma unroll
+        for (int q = 0; q < QI; ++q) {
+            const int it = tid + q * 256, r = it / (NXP / 8), x = (it - r * (NXP / 8)) * 8;
+            ok[q] = r < rows && x < nx;
+            hv[q] = load8<VEC>(Hin + (ok[q] ? base + (long)r * nx + x : base), nx - x);
+        }
+#pragma unroll
+        for (int q = 0; q < QI; ++q) {
+            const int it = tid + q * 256, r = it / (NXP / 8), x = (it - r * (NXP / 8)) * 8;
+            v8h h;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) h[i] = ok[q] ? hv[q][i] : (_Float16)0.f;
+            if (r < kRowSlab) *reinterpret_cast<v8h *>(X + r * XP + x) = h;
+        }
+    }
+    __syncthreads();
+    v4f acc[2][NJ];
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+        for (int t = 0; t < NJ; ++t) acc[rb][t] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KX; ++ks)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+            const v8h a = lds8(X + (16 * rb + lr) * XP + 32 * ks + 8 * lg);
+#pragma unroll
+            for (int t = 0; t < NJ; ++t)
+                acc[rb][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, sx[ks][t], acc[rb][t], 0, 0, 0);
+        }
+    __syncthreads();  // every wave is done reading X
+    // lane values are rows 16 rb + 4 lg + v, columns 16 (w + 4 t) + lr; staged row-major
+    if constexpr (!INV) {
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int t = 0; t < NJ; ++t)
+                if (NT % 4 == 0 || w + 4 * t < NT)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        X[(16 * rb + 4 * lg + v) * XP + 16 * (w + 4 * t) + lr] =
+                            (_Float16)acc[rb][t][v];
+        __syncthreads();
+        const int g8 = (nx + 7) / 8;
+        for (int it = tid; it < rows * g8; it += 256) {
+            const int r = it / g8, x = (it - r * g8) * 8;
+            store8<VEC>(Hout + base + (long)r * nx + x, X + r * XP + x, nx - x);
+        }
+    } else {
+        constexpr int FP = NXP + 4, QF = NT / 2;
+        float *SF = reinterpret_cast<float *>(smem);  // 32 x FP floats
+        // in FP64: sc lmin exceeds the FP32 range for residuals below ~1e-37 sqrt(Ng)
+        const float unscale =
+            (float)(1.0 / ((double)sc * (double)(p.clmin ? p.clmin[col] : p.lmin)));
+        const bool first = !PF || Pold == nullptr;
+        const float b = first ? 0.f : beta[col];
+        float vb = 0.f;
+        if constexpr (PF) vb = p.cvbar ? p.cvbar[col] : p.vbar;
+        const long pbase = (long)row0 * nx;
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int t = 0; t < NJ; ++t)
+                if (NT % 4 == 0 || w + 4 * t < NT)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        SF[(16 * rb + 4 * lg + v) * FP + 16 * (w + 4 * t) + lr] =
+                            acc[rb][t][v] * unscale;
+        __syncthreads();
+        double wz = 0.0;
+        float po[PF ? QF : 1][4], v4[PF ? QF : 1][4];
+        if constexpr (PF)
+#pragma unroll
+            for (int q = 0; q < QF; ++q) {
+                const int it = tid + q * 256, r = it / (NXP / 4), x = (it - r * (NXP / 4)) * 4;
+                const long off = r < rows && x < nx ? (long)r * nx + x : 0;
+                if (first) po[q][0] = po[q][1] = po[q][2] = po[q][3] = 0.f;
+                else load4(Pold + base + off, po[q]);
+                load4(vs + pbase + off, v4[q]);
+            }
+#pragma unroll
+        for (int q = 0; q < QF; ++q) {
+            const int it = tid + q * 256, r = it / (NXP / 4), x = (it - r * (NXP / 4)) * 4;
+            if (r >= rows || x >= nx) continue;
+            const float4 z4 = *reinterpret_cast<const float4 *>(SF + r * FP + x);
+            v4f out = {z4.x, z4.y, z4.z, z4.w};
+            if constexpr (PF) {
+                if (!first)
+                    out = v4f{z4.x + b * po[q][0], z4.y + b * po[q][1], z4.z + b * po[q][2],
+                              z4.w + b * po[q][3]};
+                wz += wz4<VEC>(v4[q], vb, z4);
+            }
+            store4<VEC>(Z + base + (long)r * nx + x, out, nx - x);
+        }
+        if constexpr (PF) {
+            // one partial per wave pair (RP / 16 = 2 per slab)
+            __shared__ double ws[4];
+            wz = wave_sum_lane63(wz);
+            if (lane == 63) ws[w] = wz;
+            __syncthreads();
+            if (tid < 2) wzp[((long)col * p.nslab + slab) * 2 + tid] = ws[2 * tid] + ws[2 * tid + 1];
         }
     }
 }
@@ -666,17 +831,17 @@ __global__ __launch_bounds__(64 * KS) __attribute__((amdgpu_waves_per_eu(KS <= 3
             const int col = (int)(job / p.npen);
             const int m = job_m(job);
             const _Float16 *src = Hin + (long)col * ld;
+            // unaligned, masked where they are staged
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    h[r][i] = (m + i < nf && s0 + r < ns) ? src[(long)(s0 + r) * nf + m + i]
-                                                          : (_Float16)0.f;
+                h[r] = (v8h)*reinterpret_cast<const v8hu *>(
+                    src + (m < nf && s0 + r < ns ? (long)(s0 + r) * nf + m : 0));
         }
     };
     // transpose a job's rows into XT: slices s0 .. s0 + 3 of rows 8 mg + i
     auto stage = [&](long job) {
-        const bool mok = job_m(job) < nf;  // nf % 8 == 0 in the vector case
+        const int left = nf - job_m(job);  // a multiple of 8 in the vector case
+        const bool mok = left > 0;
         bool ok[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) ok[r] = mok && s0 + r < ns;
@@ -684,7 +849,8 @@ __global__ __launch_bounds__(64 * KS) __attribute__((amdgpu_waves_per_eu(KS <= 3
         for (int i = 0; i < 8; ++i) {
             v4h q;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) q[r] = ok[r] ? h[r][i] : (_Float16)0.f;
+            for (int r = 0; r < 4; ++r)
+                q[r] = ok[r] && (VEC || i < left) ? h[r][i] : (_Float16)0.f;
             *reinterpret_cast<v4h *>(XT + xs + i * SP) = q;
         }
     };
@@ -820,14 +986,19 @@ __global__ __launch_bounds__(64 * KS) __attribute__((amdgpu_waves_per_eu(KS <= 3
                 for (int r = 0; r < 4; ++r)
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, z[r]), ro,
                                                            m < nf ? row_off(r) : kBufOff, 0, kBufNT);
-            } else {
+            } else if (m < nf) {
                 _Float16 *dst = Hout + (long)col * ld + m;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    if (m + i >= nf) break;
+                for (int r = 0; r < 4; ++r) {
+                    if (s0 + r >= ns) break;
+                    _Float16 *d = dst + (long)(s0 + r) * nf;
+                    if (m + 8 <= nf) {
+                        st_out(reinterpret_cast<v8hu *>(d), (v8hu)z[r]);
+                    } else {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (s0 + r < ns) dst[(long)(s0 + r) * nf + i] = z[r][i];
+                        for (int i = 0; i < 7; ++i)
+                            if (m + i < nf) d[i] = z[r][i];
+                    }
                 }
             }
         }
@@ -865,9 +1036,9 @@ void dst_plan_geometry(DstPlan &p, int dim, int nx, int ny, int nz) {
         p.ns = ny;
         p.nf = nx;
         p.NSP = p.NYP;
-        p.RP = 64;
-        p.rows = 64;
-        p.nslab = (ny + 63) / 64;
+        p.RP = kRowSlab;
+        p.rows = kRowSlab;
+        p.nslab = (ny + kRowSlab - 1) / kRowSlab;
     }
     p.npen = (p.nf + kPenMB - 1) / kPenMB;
     p.rzparts = p.npen * (p.NSP / 32);
@@ -883,9 +1054,11 @@ static bool dst_plane_sx_lds(const DstPlan &p) {
            dst_plane_xt_bytes(p) + (size_t)p.NXP * (p.NXP + 8) * 2 <= kLdsBytes;
 }
 
-// X (RP x (NXP+8) halves) and, in 3-D, TT (NXP x (NYP+8) halves), then the S_x copy; the
-// inverse pass also stages its FP32 output (RP x (NXP+4) floats) over the same space.
+// 3-D: X (RP x (NXP+8) halves), TT (NXP x (NYP+8) halves) over it, then the S_x copy; the
+// inverse pass also stages its FP32 output (RP x (NXP+4) floats) over the same space.  2-D:
+// X, and the FP32 output over it.
 size_t dst_plane_lds(const DstPlan &p, bool inv) {
+    if (p.dim == 2) return (size_t)p.RP * (inv ? (p.NXP + 4) * 4 : (p.NXP + 8) * 2);
     size_t b = dst_plane_xt_bytes(p);
     if (dst_plane_sx_lds(p)) b += (size_t)p.NXP * (p.NXP + 8) * 2;  // S_x copy
     if (inv) b = std::max(b, (size_t)(p.RP / (dst_plane_big(p) ? 2 : 1)) * (p.NXP + 4) * 4);
@@ -952,12 +1125,24 @@ hipError_t launch_pc_prep(int k, int ncols, const int *mask, PcgState s, long qs
         default: return hipErrorInvalidValue;                 \
     }
 
-// One plane-pass launch: a workgroup of 4 RP threads per (column, slab); the row-vector
-// form when rows are whole 16-byte groups, the BIG form for 3-D planes of more than 128 rows.
+// One plane-pass launch.  2-D: a workgroup of 256 threads per (column, 32 rows).  3-D: a
+// workgroup of 4 RP threads per (column, z-plane), the BIG form for planes of more than 128
+// rows.  The vector form when rows are whole 16-byte groups.
 template <typename T, bool INV, bool PF, typename... A>
 static hipError_t launch_plane(const DstPlan &p, int ncols, size_t lds, hipStream_t st, A... args) {
-    const dim3 grid((unsigned)(ncols * p.nslab)), block((unsigned)(64 * (p.RP / 16)));
     const bool vec = p.nx % 8 == 0, big = dst_plane_big(p);
+    if (p.dim == 2) {
+        const dim3 grid((unsigned)(ncols * p.nslab)), block(256);
+        if (vec) {
+            QO_DISPATCH_NT(p.NXP / 16, hipLaunchKernelGGL((k_dst_rows<T, INV, NT, true, PF>), grid,
+                                                          block, lds, st, p, args...))
+        } else {
+            QO_DISPATCH_NT(p.NXP / 16, hipLaunchKernelGGL((k_dst_rows<T, INV, NT, false, PF>), grid,
+                                                          block, lds, st, p, args...))
+        }
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)(ncols * p.nslab)), block((unsigned)(64 * (p.RP / 16)));
 #define QO_PLANE_GO(V, B)                                                                  \
     QO_DISPATCH_NT(p.NXP / 16, hipLaunchKernelGGL((k_dst_plane<T, INV, NT, V, PF, B>), grid, \
                                                   block, lds, st, p, args...))

@@ -41,6 +41,9 @@ struct Grid {
 };
 
 constexpr int kThreads = 256;
+// Values allocated past the end of every device array of a handle: kernels may read a vector
+// that begins at its last values (and drop what lies past them).
+constexpr size_t kSlack = 64;
 
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2):
 // dispatch index b runs on XCD b % 8.  Remap so that XCD x works through one
@@ -110,7 +113,7 @@ struct PcgState {
 
 // ---- fast-Poisson (DST-I) preconditioner (qo_dst.hip) ----
 // Geometry and tables of M = kappa (-Lap_h) + vbar on the column grid.  The
-// slowest axis is z in 3-D and y in 2-D; a "slab" is one z-plane (3-D) or 64
+// slowest axis is z in 3-D and y in 2-D; a "slab" is one z-plane (3-D) or 32
 // rows (2-D); a pencil workgroup covers 64 consecutive in-slice positions.
 struct DstPlan {
     int dim, nx, ny, nz;
@@ -139,6 +142,8 @@ hipError_t launch_pc_prep(int k, int ncols, const int *mask, PcgState s, long qs
 // z = M^{-1} r in three passes: forward plane (r -> t1), pencil (t1 -> t2, and the
 // partials rzp[c * rzparts + i] of r.z, summed in the spectral domain), inverse plane
 // (t2 -> z).
+// R, t1, t2, P_old and vs are read up to seven values past the end of a column (the values
+// are not used): see kSlack.
 template <typename T>
 hipError_t launch_dst_fwd(const DstPlan &p, const T *R, long ld, int ncols, _Float16 *t1,
                           const float *pcs, hipStream_t st);
