@@ -320,8 +320,8 @@ const char *qo_batch_last_error(qo_batch b);
  * sweep that starts a solve from x = 0 without reading x moves 4 of the 5 arrays of a
  * regular one and counts 0.8 of a column-iteration.  QO_KERNEL_RESID covers the FP64
  * residual passes of QO_MIXED, the ones that also apply the previous round's correction
- * x + d included.  An FP64 Jacobi solve on a grid small enough to keep a column on one CU
- * (16384 points) is one QO_KERNEL_CG_F64 launch instead of sweeps. */
+ * x + d included.  An FP64 Jacobi solve on a grid small enough to keep its columns on the
+ * chip (up to 524288 points) is a QO_KERNEL_CG_F64 launch or a few instead of sweeps. */
 typedef enum {
     QO_KERNEL_SWEEP1_F64 = 0, QO_KERNEL_SWEEP2_F64 = 1, QO_KERNEL_SWEEP1_F32 = 2,
     QO_KERNEL_SWEEP2_F32 = 3, QO_KERNEL_GRAM = 4, QO_KERNEL_UPDATE = 5, QO_KERNEL_RESID = 6,

@@ -88,7 +88,10 @@ struct qo_ctx {
     int *need = nullptr, *nneed = nullptr;
     double rel_delta = 0.1;
     bool rel = true;
-    bool colpcg = false;  // FP64 Jacobi solves take one workgroup per column
+    bool colpcg = false;  // FP64 Jacobi solves keep their columns on the CUs
+    int nclus = 0;        // clusters of workgroups, one per column; 0: a workgroup per column
+    int *cluctl = nullptr;
+    double *cluslot = nullptr;
     int colchunk = 8192;  // iterations per launch of that form
     // fast-Poisson preconditioner (precond == 1)
     bool dst = false;
@@ -440,21 +443,46 @@ qo_status precondition_p(qo_ctx *c, const float *R, const float *Pold, float *Pn
     return QO_OK;
 }
 
-// FP64 Jacobi-PCG with a workgroup per column (launch_pcg_column): one launch for the whole
-// solve, continued every colchunk iterations so that no launch runs unboundedly long when
-// pcg_maxit is large.  Counts and states are written straight to pinned host memory.
-qo_status pcg_column(qo_ctx *c, const double *B, double *X, int ncols, int use_x0, double tol,
-                     int *its_out, const char *what) {
+// FP64 Jacobi-PCG with a workgroup (launch_pcg_column) or a cluster of workgroups
+// (launch_pcg_cluster) per column: one launch for the whole solve, continued every colchunk
+// iterations so that no launch runs unboundedly long when pcg_maxit is large (and cut into
+// ranges of columns, eight per cluster).  Counts and states are written straight to pinned
+// host memory.  *stalled: a cluster's wait ran out (nothing else is reported then).
+qo_status pcg_onchip(qo_ctx *c, const double *B, double *X, int ncols, int use_x0, double tol,
+                     int *its_out, const char *what, bool *stalled) {
     hipStream_t st = c->st;
-    int *its = poll_slot(c, 0), *state = poll_slot(c, 1);
+    int *its = poll_slot(c, 0), *state = poll_slot(c, 1), *ctl = round_slot(c);
     const int maxit = c->cfg.pcg_maxit;
+    // Grids that fit one workgroup too (8193 .. 16384 points): a cluster of two iterates in about
+    // 9 us against 13, unless more columns than clusters are to be solved (128^2: 64 columns
+    // 3.9 against 5.6 ms, 256 columns 7.7 against 6.9 ms).
+    const bool clusters = c->nclus > 0 && !(pcg_column_fits(c->g) && ncols > c->nclus);
+    const int range = clusters ? 8 * c->nclus : ncols;
+    *stalled = false;
     int running = 0;
     for (int k0 = 0;;) {
         const int kend = maxit - k0 > c->colchunk ? k0 + c->colchunk : maxit;
-        hipEvent_t e = prof_begin(c);
-        HIPC(c, launch_pcg_column(c->g, c->vs, c->dinv, B, X, c->r, c->pa, c->ld, ncols, use_x0, tol,
-                                  k0, kend, kend == maxit, c->part, its, state, st));
-        prof_end(c, QO_KERNEL_CG_F64, e);
+        const bool last = kend == maxit;
+        for (int c0 = 0; c0 < ncols; c0 += range) {
+            hipEvent_t e = prof_begin(c);
+            if (clusters)
+                HIPC(c, launch_pcg_cluster(c->g, c->nclus, c->vs, c->dinv, B, X, c->r, c->pa, c->pb,
+                                           c->ld, c0, std::min(ncols, c0 + range), use_x0, tol, k0,
+                                           kend, last, c->part, its, state, c->cluctl, c->cluslot,
+                                           st));
+            else
+                HIPC(c, launch_pcg_column(c->g, c->vs, c->dinv, B, X, c->r, c->pa, c->ld, ncols,
+                                          use_x0, tol, k0, kend, last, c->part, its, state, st));
+            prof_end(c, QO_KERNEL_CG_F64, e);
+            if (clusters) {
+                HIPC(c, hipMemcpyAsync(ctl, c->cluctl, sizeof(int), hipMemcpyDeviceToHost, st));
+                HIPC(c, hipStreamSynchronize(st));
+                if (ctl[0]) {
+                    *stalled = true;
+                    return QO_OK;
+                }
+            }
+        }
         HIPC(c, hipStreamSynchronize(st));
         prof_harvest(c);
         running = 0;
@@ -466,7 +494,7 @@ qo_status pcg_column(qo_ctx *c, const double *B, double *X, int ncols, int use_x
             code = std::max(code, state[j]);
         }
         if (code) return check_poll_err(c, code, col, what);
-        if (running == 0 || kend == maxit) break;
+        if (running == 0 || last) break;
         k0 = kend;
     }
     if (running)
@@ -508,7 +536,14 @@ qo_status pcg(qo_ctx *c, const T *vs, const T *dinv, const T *B, T *X, T *R, T *
               const RoundPoll *outer = nullptr, bool *outer_done = nullptr,
               int *its_async = nullptr) {
     if constexpr (sizeof(T) == 8)
-        if (c->colpcg) return pcg_column(c, B, X, ncols, use_x0, tol, its_out, what);
+        if (c->colpcg) {
+            bool stalled = false;
+            const qo_status s_ = pcg_onchip(c, B, X, ncols, use_x0, tol, its_out, what, &stalled);
+            if (!stalled) return s_;
+            // the streaming sweeps from what X holds, for good (the workspace they need is
+            // there in any case)
+            c->colpcg = false;
+        }
     const Grid &g = c->g;
     hipStream_t st = c->st;
     PcgState s = c->ps;
@@ -1675,8 +1710,14 @@ qo_status qo_create(const qo_config *cfg, void *hip_stream, qo_handle *out) {
     h->rel = env_int("QO_MIXED_RESTART", 0) == 0;
     if (const char *d = getenv("QO_REL_DELTA")) h->rel_delta = atof(d);
     // a forced tiling asks for the streaming sweeps
-    h->colpcg = !h->mixed && c.precond == 0 && pcg_column_fits(h->g) && !getenv("QO_TY") &&
-                !getenv("QO_ZC");
+    if (!h->mixed && c.precond == 0 && c.pcg_variant != 1 && !getenv("QO_TY") && !getenv("QO_ZC")) {
+        if (s == QO_OK && pcg_cluster_width(h->g) > 1) h->nclus = pcg_cluster_count(h->g);
+        h->colpcg = h->nclus > 0 || pcg_column_fits(h->g);
+        if (h->nclus > 0) {
+            A(&h->cluctl, pcg_cluster_ints());
+            A(&h->cluslot, pcg_cluster_slots());
+        }
+    }
     h->colchunk = std::max(1, env_int("QO_COL_CHUNK", h->colchunk));
     A(&h->nact, 1);
     A(&h->dstatus, 1);

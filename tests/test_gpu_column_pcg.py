@@ -1,5 +1,6 @@
-"""The workgroup-per-column form of the FP64 Jacobi-PCG (small grids) against the oracle's
-PCG, at the edges of its point counts and thread shapes.
+"""The FP64 Jacobi-PCG forms that keep a column on the chip, one workgroup or a cluster of
+workgroups per column, against the oracle's PCG, at the edges of their point counts and
+thread shapes.
 
 Tolerance: both solve to ||r|| <= 1e-12 ||b|| by the same iteration; x differs by at most
 about 2e-12 ||b|| / lambda_min, and lambda_min ||x|| >= 1e-2 ||b|| is checked for the random
@@ -28,7 +29,11 @@ def _binding():
 GRIDS = [(2, (1, 2)), (2, (5, 1)), (2, (32, 32)), (2, (25, 41)), (2, (1024, 2)), (2, (64, 33)),
          (2, (128, 32)), (2, (17, 241)), (2, (128, 64)), (2, (113, 73)), (2, (128, 128)),
          (3, (8, 8, 16)), (3, (7, 13, 12)), (3, (16, 16, 16)), (3, (3, 5, 300)), (3, (20, 20, 20)),
-         (3, (21, 23, 17)), (3, (16, 32, 32)), (3, (25, 25, 26)), (3, (1, 1, 9))]
+         (3, (21, 23, 17)), (3, (16, 32, 32)), (3, (25, 25, 26)), (3, (1, 1, 9)),
+         # several workgroups per column: two, a ragged last one, planes larger than a range's
+         # half, many (slabs of less than a plane), the most a column takes
+         (2, (91, 90)), (2, (129, 127)), (2, (199, 199)), (3, (33, 31, 9)), (3, (75, 77, 5)),
+         (3, (64, 64, 33)), (3, (70, 70, 40)), (3, (64, 64, 128))]
 
 
 @pytest.mark.parametrize("dim,n", GRIDS, ids=["x".join(map(str, n)) for _, n in GRIDS])
@@ -55,7 +60,7 @@ def test_column_solve(oracle_mod, dim, n):
         assert not X.any() and not it.any()
 
 
-@pytest.mark.parametrize("n", [(20, 17), (100, 90)])
+@pytest.mark.parametrize("n", [(20, 17), (100, 90), (150, 160)])
 def test_column_solve_continued_and_limits(n):
     """A solve cut into launches of three iterations gives the same bits as one launch; the
     iteration limit and non-finite input are reported."""
@@ -90,3 +95,43 @@ def test_column_solve_continued_and_limits(n):
         with pytest.raises(B.QOError) as e:
             s.solve(bad)
         assert e.value.status == B.QO_ERR_NONFINITE and "column 1" in str(e.value)
+
+
+def test_concurrent_handles():
+    """Two handles on two streams, driven by two threads at once, give the bits they give
+    alone (clusters of workgroups wait for one another inside a launch)."""
+    import threading
+
+    import torch
+
+    B = _binding()
+    n, N = (40, 40, 40), 24
+    rng = np.random.default_rng(3)
+    V = 30.0 * rng.random(n[0] * n[1] * n[2])
+    blocks = [B.as_block(np.asfortranarray(rng.standard_normal((N, V.size)).T)) for _ in range(2)]
+    torch.cuda.synchronize()
+    solvers = []
+    for _ in range(2):
+        s = B.Solver(3, n, N, pcg_tol=1e-10, stream=torch.cuda.Stream())
+        s.set_potential(V)
+        solvers.append(s)
+    alone = [B.to_numpy(s.solve(b)[0]) for s, b in zip(solvers, blocks)]
+    got = [[], []]
+
+    def work(i):
+        with torch.cuda.stream(solvers[i].stream):
+            for _ in range(4):
+                X = torch.zeros_like(blocks[i])
+                solvers[i].stream.synchronize()
+                got[i].append(solvers[i].solve(blocks[i], X)[0])
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for i in range(2):
+        for X in got[i]:
+            assert np.array_equal(B.to_numpy(X), alone[i])
+        solvers[i].close()
