@@ -204,10 +204,11 @@ __device__ __forceinline__ void gram_rows(const double *const (&pa_)[4],
 // chunk costs one partial instead of one per wavefront (with one wavefront per chunk the
 // partials of 96 columns at 64^3 rows were 75 MB written and read against 201 MB of
 // operands).  W = 1 (many tile pairs): the wavefronts of a CU are different tile pairs of
-// the same rows and share them in the caches (512 columns at 96^3 rows: 4.60 ms with W = 4).  16 x 16 blocks past the last column, or below the diagonal of a diagonal
-// tile, are not computed (an FP64 MFMA occupies its matrix core for 64 cycles, and with 96
-// columns 27 of 48 blocks are of that kind): the tile's extent selects a form whose loops
-// hold its blocks alone.
+// the same rows and share them in the caches (512 columns at 96^3 rows: 4.60 ms with
+// W = 4).  16 x 16 blocks past the last column, or below the diagonal of a diagonal tile,
+// are not computed (an FP64 MFMA occupies its matrix core for 64 cycles, and with 96 columns
+// 27 of 48 blocks are of that kind): the tile's extent selects a form whose loops hold its
+// blocks alone.
 // CROSS: the n x n block X^T Y alone (tile (ti, tj) = pair / ntn, pair % ntn over X
 // columns x Y columns), partials n x n per split.
 template <int W, bool CROSS = false>
@@ -261,7 +262,11 @@ __device__ __forceinline__ void gram_f64_tile(const double *__restrict__ X,
         else QO_GRAM(4, 4, false, false);
     } else if (CROSS) {
         QO_GRAM(4, 4, false, true);
-    } else if (ti == tj) {
+    } else if (ti == tj && (W != 1 || nt < 7)) {
+        // From 28 tile pairs on (W = 1) diagonal tiles are computed whole: their wavefronts
+        // would run ahead of the others on the same rows, which then meet in the caches less
+        // often (trimmed against whole, 512 columns at 96^3 rows: 4.81 and 4.59 ms; with 15
+        // pairs the work saved weighs more, 320 columns at 64^3 rows: 0.76 and 0.81 ms).
         if (nj == 4) QO_GRAM(4, 4, true, true);
         else if (nj == 3) QO_GRAM(3, 3, true, true);
         else if (nj == 2) QO_GRAM(2, 2, true, true);
