@@ -47,6 +47,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #ifndef QO_PLANE_ALIAS
 #define QO_PLANE_ALIAS 1
@@ -196,19 +197,25 @@ __host__ __device__ inline size_t dst_plane_xt_bytes(const DstPlan &p) {
     return (b + 15) & ~(size_t)15;
 }
 
-// Four values from src on (element-aligned) ...
+// Four values from src on (ALL: 16-byte aligned groups; else element-aligned) ...
+template <bool ALL>
 __device__ __forceinline__ void load4(const float *src, float (&v)[4]) {
-    const v4fu a = *reinterpret_cast<const v4fu *>(src);
+    using V = std::conditional_t<ALL, v4f, v4fu>;
+    const V a = *reinterpret_cast<const V *>(src);
     v[0] = a[0]; v[1] = a[1]; v[2] = a[2]; v[3] = a[3];
 }
+template <bool ALL>
 __device__ __forceinline__ void load4(const double *src, double (&v)[4]) {
-    const v2du a = reinterpret_cast<const v2du *>(src)[0], b = reinterpret_cast<const v2du *>(src)[1];
+    using V = std::conditional_t<ALL, v2d, v2du>;
+    const V a = reinterpret_cast<const V *>(src)[0], b = reinterpret_cast<const V *>(src)[1];
     v[0] = a[0]; v[1] = a[1]; v[2] = b[0]; v[3] = b[1];
 }
-// ... and the first min(4, left) of v to dst (ALL: left >= 4).
+// ... and the first min(4, left) of v to dst.
 template <bool ALL>
 __device__ __forceinline__ void store4(float *dst, v4f v, int left) {
-    if (ALL || left >= 4) {
+    if constexpr (ALL) {
+        st_out(reinterpret_cast<v4f *>(dst), v);
+    } else if (left >= 4) {
         st_out(reinterpret_cast<v4fu *>(dst), (v4fu)v);
     } else {
 #pragma unroll
@@ -338,7 +345,7 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
             const int r = it / (NXP / 4);
             const int x = (it - r * (NXP / 4)) * 4;
             okq[q] = r < rows && x < nx;
-            load4(R + (okq[q] ? base + (long)r * nx + x : base), rv[q]);
+            load4<VEC>(R + (okq[q] ? base + (long)r * nx + x : base), rv[q]);
         }
     } else {
 #pragma unroll
@@ -398,13 +405,19 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
     const int w = tid >> 6, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
     const int KX = NXP / 32;
     // this wave's rows of S_y (the A operand of the y-transform; NYP <= 32 KYM in 3-D),
-    // loaded now so that their latency overlaps the x-transform
+    // loaded now so that their latency overlaps the x-transform.  The scheduling barriers
+    // keep them between the slab's staging and the product: moved into either they cost
+    // 10 registers and, at 96 points a side, two of the eight waves per SIMD (183 against
+    // 171 us per inverse pass of 256 columns).  Planes beyond 128 points have four waves per
+    // SIMD either way and are faster when the loads may move (192: 438 against 461 us).
     constexpr int KYM = BIG ? 8 : 4;
     v8h ay[KYM];
+    if constexpr (!BIG) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks = 0; ks < KYM; ++ks)
         ay[ks] = *reinterpret_cast<const v8h *>(
             p.Sy + (16 * w + lr) * p.NYP + 32 * min(ks, p.NYP / 32 - 1) + 8 * lg);
+    if constexpr (!BIG) __builtin_amdgcn_sched_barrier(0);
     v4f acc[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -501,8 +514,8 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
                     const bool ok = rl < hrows && x < nx;
                     const long off = ok ? (long)(r0 + rl) * nx + x : 0;
                     if (first) po[q][0] = po[q][1] = po[q][2] = po[q][3] = 0.f;
-                    else load4(Pold + base + off, po[q]);
-                    load4(vs + pbase + off, v4[q]);
+                    else load4<VEC>(Pold + base + off, po[q]);
+                    load4<VEC>(vs + pbase + off, v4[q]);
                 }
 #pragma unroll
                 for (int q = 0; q < QH; ++q) {
@@ -581,7 +594,7 @@ __global__ __launch_bounds__(256) void k_dst_rows(DstPlan p, const T *__restrict
         for (int q = 0; q < QF; ++q) {
             const int it = tid + q * 256, r = it / (NXP / 4), x = (it - r * (NXP / 4)) * 4;
             ok[q] = r < rows && x < nx;
-            load4(R + (ok[q] ? base + (long)r * nx + x : base), rv[q]);
+            load4<VEC>(R + (ok[q] ? base + (long)r * nx + x : base), rv[q]);
         }
 #pragma unroll
         for (int q = 0; q < QF; ++q) {
@@ -674,8 +687,8 @@ __global__ __launch_bounds__(256) void k_dst_rows(DstPlan p, const T *__restrict
                 const int it = tid + q * 256, r = it / (NXP / 4), x = (it - r * (NXP / 4)) * 4;
                 const long off = r < rows && x < nx ? (long)r * nx + x : 0;
                 if (first) po[q][0] = po[q][1] = po[q][2] = po[q][3] = 0.f;
-                else load4(Pold + base + off, po[q]);
-                load4(vs + pbase + off, v4[q]);
+                else load4<VEC>(Pold + base + off, po[q]);
+                load4<VEC>(vs + pbase + off, v4[q]);
             }
 #pragma unroll
         for (int q = 0; q < QF; ++q) {
