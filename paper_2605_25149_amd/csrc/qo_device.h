@@ -8,40 +8,6 @@
 namespace qo {
 namespace dev {
 
-struct Red {
-    double v[4][kThreads / 64];
-};
-
-template <int NQ>
-__device__ __forceinline__ void block_sums(double (&v)[NQ], Red &red) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[q] += __shfl_xor(v[q], off, 64);
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0)
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) red.v[q][wid] = v[q];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        double s = 0.0;
-#pragma unroll
-        for (int w = 0; w < kThreads / 64; ++w) s += red.v[q][w];
-        v[q] = s;
-    }
-}
-
-// Sum of part[c*tiles + t] over t, identical in every thread and every block.
-__device__ __forceinline__ double col_sum(const double *__restrict__ part, int c, int tiles,
-                                          Red &red) {
-    double s[1] = {0.0};
-    for (int t = threadIdx.x; t < tiles; t += kThreads) s[0] += part[(long)c * tiles + t];
-    block_sums<1>(s, red);
-    return s[0];
-}
-
 // Sum of v over the 64 lanes of a wavefront, complete in lane 63, by DPP moves (no LDS
 // traffic, no address registers): pairs and quads by quad permutations, rows of 16 by
 // row shifts, then the row sums carried up by the row broadcasts of 15 and 31.  A lane
@@ -78,6 +44,38 @@ __device__ __forceinline__ double wave_sum_lane63(double v) {
     return v;
 }
 
+struct Red {
+    double v[4][kThreads / 64];
+};
+
+template <int NQ>
+__device__ __forceinline__ void block_sums(double (&v)[NQ], Red &red) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) v[q] = wave_sum_lane63(v[q]);
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    __syncthreads();
+    if (lane == 63)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) red.v[q][wid] = v[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) s += red.v[q][w];
+        v[q] = s;
+    }
+}
+
+// Sum of part[c*tiles + t] over t, identical in every thread and every block.
+__device__ __forceinline__ double col_sum(const double *__restrict__ part, int c, int tiles,
+                                          Red &red) {
+    double s[1] = {0.0};
+    for (int t = threadIdx.x; t < tiles; t += kThreads) s[0] += part[(long)c * tiles + t];
+    block_sums<1>(s, red);
+    return s[0];
+}
+
 // Sum of lanes 0..15, in every lane (the other lanes' values do not count).
 __device__ __forceinline__ double row_sum16(double v) {
     v += dpp_move_d<0xb1>(v);
@@ -88,6 +86,19 @@ __device__ __forceinline__ double row_sum16(double v) {
     const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)b, 15);
     const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), 15);
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Several such sums at once: v[q] = sum of p[q][0 .. n[q] - 1].  Their loads are under way
+// together and they share one reduction.
+template <int NQ>
+__device__ __forceinline__ void part_sums(const double *const (&p)[NQ], const int (&n)[NQ],
+                                          double (&v)[NQ], Red &red) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        v[q] = 0.0;
+        for (int t = threadIdx.x; t < n[q]; t += kThreads) v[q] += p[q][t];
+    }
+    block_sums<NQ>(v, red);
 }
 
 // Round an FP64 value to bfloat16, nearest-even on the 45 dropped mantissa bits (one

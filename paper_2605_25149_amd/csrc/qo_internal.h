@@ -195,7 +195,7 @@ hipError_t launch_pcg_sweep1(const Grid &g, const T *vs, const T *dinv, const T 
                              const T *Pold, T *Pnew, long ld, int ncols, int k, double tol,
                              const int *mask, PcgState s, hipStream_t st,
                              const float *Z = nullptr, const double *rzp = nullptr,
-                             int rzt = 0, bool p_given = false);
+                             int rzt = 0);
 template <typename T>
 // xzero: X is zero on entry (first iteration without an init pass; preconditioned form
 // only): X = alpha p is written without reading X.

@@ -23,6 +23,8 @@
 #include "qo_internal.h"
 #include "qo_device.h"
 
+#include <type_traits>
+
 #ifndef QO_SWEEP2_NT
 #define QO_SWEEP2_NT 1
 #endif
@@ -45,10 +47,10 @@ using dev::col_sum;
 // is issued under the tile's own bounds, which keeps the registers of those many points
 // per thread low; with one plane per tile the loop below runs once and nothing is
 // carried across planes.
-template <typename T, int PPT, class Ld, class Ep>
-__device__ __forceinline__ void engine_wide(const Grid &g, int band, int zc,
+template <typename T, int PPT, class Ld, class Ep, class Pre>
+__device__ __forceinline__ bool engine_wide(const Grid &g, int band, int zc,
                                             const T *__restrict__ vs, Ld &ld, Ep &ep,
-                                            T *__restrict__ lds) {
+                                            T *__restrict__ lds, Pre &pre) {
     using LR = typename Ld::Raw;
     using ER = typename Ep::Raw;
     const int tid = threadIdx.x;
@@ -77,19 +79,17 @@ __device__ __forceinline__ void engine_wide(const Grid &g, int band, int zc,
     ER er[PPT];
     LR hlo = Ld::zero(), hhi = Ld::zero();
     const long b0 = (long)z0 * plane + (long)y0 * nx;
-    // prologue: operands of planes z0-1, z0 (with halo rows), z0+1
+    // operands of planes z0-1, z0 (with halo rows), z0+1
+    LR rm[PPT], rc[PPT], rp[PPT], rlo = Ld::zero(), rhi = Ld::zero();
 #pragma unroll
     for (int s = 0; s < PPT; ++s) {
         const int t = tid + s * kThreads;
-        om[s] = (val[s] && z0 > 0) ? ld.make(ld.load(b0 - plane + t)) : T(0);
-        oc[s] = val[s] ? ld.make(ld.load(b0 + t)) : T(0);
-        op[s] = (val[s] && z0 + 1 < nz) ? ld.make(ld.load(b0 + plane + t)) : T(0);
-        if (val[s]) lds[nx + t] = oc[s];
+        rm[s] = (val[s] && z0 > 0) ? ld.load(b0 - plane + t) : Ld::zero();
+        rc[s] = val[s] ? ld.load(b0 + t) : Ld::zero();
+        rp[s] = (val[s] && z0 + 1 < nz) ? ld.load(b0 + plane + t) : Ld::zero();
     }
-    for (int hh = tid; hh < nx; hh += kThreads) {
-        lds[hh] = has_lo ? ld.make(ld.load(b0 + lo_off + hh)) : T(0);
-        lds[(ty + 1) * nx + hh] = has_hi ? ld.make(ld.load(b0 + hi_off + hh)) : T(0);
-    }
+    if (hown && has_lo) rlo = ld.load(b0 + lo_off + tid);
+    if (hown && has_hi) rhi = ld.load(b0 + hi_off + tid);
     // prefetch for the first iteration
 #pragma unroll
     for (int s = 0; s < PPT; ++s) {
@@ -101,6 +101,23 @@ __device__ __forceinline__ void engine_wide(const Grid &g, int band, int zc,
     if (hown && z0 + 1 < z1) {
         if (has_lo) hlo = ld.load(b0 + plane + lo_off + tid);
         if (has_hi) hhi = ld.load(b0 + plane + hi_off + tid);
+    }
+    if (!pre()) return false;
+#pragma unroll
+    for (int s = 0; s < PPT; ++s) {
+        const int t = tid + s * kThreads;
+        om[s] = (val[s] && z0 > 0) ? ld.make(rm[s]) : T(0);
+        oc[s] = val[s] ? ld.make(rc[s]) : T(0);
+        op[s] = (val[s] && z0 + 1 < nz) ? ld.make(rp[s]) : T(0);
+        if (val[s]) lds[nx + t] = oc[s];
+    }
+    if (hown) {
+        lds[tid] = has_lo ? ld.make(rlo) : T(0);
+        lds[(ty + 1) * nx + tid] = has_hi ? ld.make(rhi) : T(0);
+    }
+    for (int hh = tid + kThreads; hh < nx; hh += kThreads) {  // nx > 256 only
+        lds[hh] = has_lo ? ld.make(ld.load(b0 + lo_off + hh)) : T(0);
+        lds[(ty + 1) * nx + hh] = has_hi ? ld.make(ld.load(b0 + hi_off + hh)) : T(0);
     }
     __syncthreads();
     for (int z = z0; z < z1; ++z) {
@@ -159,7 +176,13 @@ __device__ __forceinline__ void engine_wide(const Grid &g, int band, int zc,
         }
         __syncthreads();
     }
+    return true;
 }
+
+// No scalars to wait for.
+struct PreNone {
+    __device__ bool operator()() const { return true; }
+};
 
 // The streaming engine.
 //
@@ -171,14 +194,17 @@ __device__ __forceinline__ void engine_wide(const Grid &g, int band, int zc,
 // z+2, and of V+sigma and the epilogue inputs of plane z+1 are in flight.  The
 // per-plane barrier waits on LDS only, so those loads overlap the barrier and
 // the next plane's arithmetic instead of stalling each plane.
-template <typename T, int PPT, bool PP = true, class Ld, class Ep>
-__device__ __forceinline__ void engine(const Grid &g, int band, int zc,
+//
+//   Pre: the tile's scalars.  pre() is called once the first loads have been issued and
+//        before any of them is used (it may hold barriers); it sets what ld.make and ep need
+//        (beta, alpha) and says whether the tile is to be worked at all.  The reductions
+//        behind the scalars then overlap the first loads' latency, which on small grids
+//        is most of a sweep.
+template <typename T, int PPT, bool PP = true, class Ld, class Ep, class Pre>
+__device__ __forceinline__ bool engine(const Grid &g, int band, int zc,
                                        const T *__restrict__ vs, Ld &ld, Ep &ep,
-                                       T *__restrict__ lds) {
-    if constexpr (PPT >= 4) {
-        engine_wide<T, PPT>(g, band, zc, vs, ld, ep, lds);
-        return;
-    }
+                                       T *__restrict__ lds, Pre &pre) {
+    if constexpr (PPT >= 4) return engine_wide<T, PPT>(g, band, zc, vs, ld, ep, lds, pre);
     using LR = typename Ld::Raw;
     using ER = typename Ep::Raw;
     const int tid = threadIdx.x;
@@ -213,20 +239,7 @@ __device__ __forceinline__ void engine(const Grid &g, int band, int zc,
         LR hlo, hhi;  // halo rows of the plane staged next
     } pa, pb;
     const long b0 = (long)z0 * plane + (long)y0 * nx;
-    // prologue: operands of planes z0-1, z0 (with halo rows), z0+1
-#pragma unroll
-    for (int s = 0; s < PPT; ++s) {
-        const int t = tid + s * kThreads;
-        om[s] = (val[s] && z0 > 0) ? ld.make(ld.load(b0 - plane + t)) : T(0);
-        oc[s] = val[s] ? ld.make(ld.load(b0 + t)) : T(0);
-        op[s] = (val[s] && z0 + 1 < nz) ? ld.make(ld.load(b0 + plane + t)) : T(0);
-        if (val[s]) lds[nx + t] = oc[s];
-    }
-    for (int hh = tid; hh < nx; hh += kThreads) {
-        lds[hh] = has_lo ? ld.make(ld.load(b0 + lo_off + hh)) : T(0);
-        lds[(ty + 1) * nx + hh] = has_hi ? ld.make(ld.load(b0 + hi_off + hh)) : T(0);
-    }
-    // Every load from here on is unconditional: a point past the tile's end reads the
+    // Every load is unconditional: a point past the tile's end reads the
     // tile's first point, a plane past the column's end reads the last plane, a halo row
     // that does not exist reads the tile's own row (halo columns past nx: column 0), and
     // the value is dropped at its use.  (Lane offsets below 256 * PPT let the loads take
@@ -253,7 +266,52 @@ __device__ __forceinline__ void engine(const Grid &g, int band, int zc,
         f.hlo = ld.load(bh + hlo_off + hx);
         f.hhi = ld.load(bh + hhi_off + hx);
     };
-    prefetch(z0 - 1, pa);
+    // operands of planes z0-1, z0 (with halo rows), z0+1
+    if constexpr (std::is_same_v<Pre, PreNone>) {
+        // nothing to wait for but the loads: staged before the prefetch, which would cost
+        // registers beside them (and k_apply, with 99 instead of 95, a wave per SIMD)
+#pragma unroll
+        for (int s = 0; s < PPT; ++s) {
+            const int t = tid + s * kThreads;
+            om[s] = (val[s] && z0 > 0) ? ld.make(ld.load(b0 - plane + t)) : T(0);
+            oc[s] = val[s] ? ld.make(ld.load(b0 + t)) : T(0);
+            op[s] = (val[s] && z0 + 1 < nz) ? ld.make(ld.load(b0 + plane + t)) : T(0);
+            if (val[s]) lds[nx + t] = oc[s];
+        }
+        for (int hh = tid; hh < nx; hh += kThreads) {
+            lds[hh] = has_lo ? ld.make(ld.load(b0 + lo_off + hh)) : T(0);
+            lds[(ty + 1) * nx + hh] = has_hi ? ld.make(ld.load(b0 + hi_off + hh)) : T(0);
+        }
+        prefetch(z0 - 1, pa);
+    } else {
+        LR rm[PPT], rc[PPT], rp[PPT];
+        const long bm = (long)max(z0 - 1, 0) * plane + yb;
+        const long bp = (long)min(z0 + 1, nz - 1) * plane + yb;
+#pragma unroll
+        for (int s = 0; s < PPT; ++s) {
+            rm[s] = ld.load(bm + tc[s]);
+            rc[s] = ld.load(b0 + tc[s]);
+            rp[s] = ld.load(bp + tc[s]);
+        }
+        const LR rlo = ld.load(b0 + hlo_off + hx), rhi = ld.load(b0 + hhi_off + hx);
+        prefetch(z0 - 1, pa);
+        if (!pre()) return false;
+#pragma unroll
+        for (int s = 0; s < PPT; ++s) {
+            om[s] = (val[s] && z0 > 0) ? ld.make(rm[s]) : T(0);
+            oc[s] = val[s] ? ld.make(rc[s]) : T(0);
+            op[s] = (val[s] && z0 + 1 < nz) ? ld.make(rp[s]) : T(0);
+            if (val[s]) lds[nx + tid + s * kThreads] = oc[s];
+        }
+        if (hown) {
+            lds[tid] = has_lo ? ld.make(rlo) : T(0);
+            lds[(ty + 1) * nx + tid] = has_hi ? ld.make(rhi) : T(0);
+        }
+        for (int hh = tid + kThreads; hh < nx; hh += kThreads) {  // nx > 256 only
+            lds[hh] = has_lo ? ld.make(ld.load(b0 + lo_off + hh)) : T(0);
+            lds[(ty + 1) * nx + hh] = has_hi ? ld.make(ld.load(b0 + hi_off + hh)) : T(0);
+        }
+    }
     __syncthreads();
     // the stencil at plane z from LDS buffer L and the z-registers, and the epilogue
     auto plane_out = [&](int z, const T *__restrict__ L, const Pf &cu) {
@@ -275,7 +333,7 @@ __device__ __forceinline__ void engine(const Grid &g, int band, int zc,
     if (z1 - z0 == 1) {  // a single plane (2-D grids)
         plane_out(z0, lds, pa);
         __syncthreads();
-        return;
+        return true;
     }
     // Plane z (epilogue only when live), then plane z+1 staged into the other LDS buffer,
     // the z-registers moved on, and the next loads issued into set nx_.
@@ -325,6 +383,15 @@ __device__ __forceinline__ void engine(const Grid &g, int band, int zc,
             step(z + 1, z + 1 < z1, pb, pa);
         }
     }
+    return true;
+}
+
+template <typename T, int PPT, bool PP = true, class Ld, class Ep>
+__device__ __forceinline__ void engine(const Grid &g, int band, int zc,
+                                       const T *__restrict__ vs, Ld &ld, Ep &ep,
+                                       T *__restrict__ lds) {
+    PreNone pre;
+    engine<T, PPT, PP>(g, band, zc, vs, ld, ep, lds, pre);
 }
 
 // ---- operand loaders and epilogue building blocks
@@ -680,29 +747,20 @@ struct EpSweep1 {
     }
 };
 
-// MODE 0: Jacobi, z = D r formed on the fly, r.z from sweep2's partials.
-// MODE 1: the preconditioned residual z is an input (fast-Poisson preconditioner) and
-//         r.z comes from the preconditioner's partials rzp (rzt per column).
-// MODE 2: as 1, but the inverse preconditioner pass has already formed p = z + beta p_old
-//         (in Pnew) and r.z per column is rzp[c] (rzt == 1): the sweep only reads p for
-//         gamma and the bookkeeping; nothing is stored.
+// XZ false: Jacobi, z = D r formed on the fly, r.z from sweep2's partials.
+// XZ true: the preconditioned residual z is an input (fast-Poisson preconditioner) and
+//          r.z comes from the preconditioner's partials rzp (rzt per column).
 // FP32 with z as input at 3 points per thread: capped to six waves per SIMD, which spills
 // a few registers of the two prefetch sets and is still faster than the five waves that
 // fit without spills (96^3 x 256: 423 against 456 us).
-template <typename T, int PPT, int MODE>
+template <typename T, int PPT, bool XZ>
 __global__ __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && MODE == 1 && PPT == 3 ? 6 : 1))) void k_pcg_sweep1(Grid g, const T *__restrict__ vs,
-                                                         const T *__restrict__ dinv,
-                                                         const T *__restrict__ R,
-                                                         const T *__restrict__ Pold,
-                                                         T *__restrict__ Pnew, long ld, int ncols,
-                                                         int k, double tol,
-                                                         const int *__restrict__ mask,
-                                                         PcgState s, long qs,
-                                                         const float *__restrict__ Z,
-                                                         const double *__restrict__ rzp, int rzt) {
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && XZ && PPT == 3 ? 6 : 1))) void k_pcg_sweep1(
+    Grid g, const T *__restrict__ vs, const T *__restrict__ dinv, const T *__restrict__ R,
+    const T *__restrict__ Pold, T *__restrict__ Pnew, long ld, int ncols, int k, double tol,
+    const int *__restrict__ mask, PcgState s, long qs, const float *__restrict__ Z,
+    const double *__restrict__ rzp, int rzt) {
     __shared__ Red red;
-    __shared__ int sh_flag;
     int col, tile, band, zc;
     tile_of(g, col, tile, band, zc);
     vs = col_pt(g, vs, col);
@@ -715,63 +773,47 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && MODE == 1 && PPT == 3 ? 6 :
         if (lead && threadIdx.x == 0) s.active[cur * ncols + col] = 0;
         return;
     }
-    const double rr = col_sum(s.part + qs, col, tiles, red);
-    double bb;
-    if (k == 0) {
-        bb = col_sum(s.part + 2 * qs, col, tiles, red);
-        if (lead && threadIdx.x == 0) s.bb[col] = bb;
-    } else {
-        bb = s.bb[col];
-    }
-    const double ctol = s.coltol ? s.coltol[col] : tol;
-    // the convergence test first: a converged column's z is not computed
-    const bool conv = sqrt(rr) <= ctol * sqrt(bb);
-    constexpr bool XZ = MODE != 0;
-    const double rz = (XZ && conv) ? 0.0
-                      : MODE == 2 ? rzp[col]
-                      : (XZ ? col_sum(rzp, col, rzt, red) : col_sum(s.part, col, tiles, red));
-    if (threadIdx.x == 0) {
-        int flag = 0;  // 0 run, 1 converged, 2 non-finite
-        if (!isfinite(rz) || !isfinite(rr) || !isfinite(bb)) flag = 2;
-        else if (conv) flag = 1;
-        sh_flag = flag;
-        if (lead) {
+    const long pc = (long)col * tiles;
+    const double rho_old = k == 0 ? 0.0 : s.rho[prv * ncols + col];
+    const double bb_old = k == 0 ? 0.0 : s.bb[col];
+    // the column's sums, the stop test and beta (the same in every thread)
+    auto scalars = [&](T &beta) {
+        const double *const ps[3] = {s.part + qs + pc, XZ ? rzp + (long)col * rzt : s.part + pc,
+                                     s.part + 2 * qs + pc};
+        const int n[3] = {tiles, XZ ? rzt : tiles, k == 0 ? tiles : 0};
+        double v[3];
+        dev::part_sums<3>(ps, n, v, red);
+        const double rr = v[0], bb = k == 0 ? v[2] : bb_old;
+        const double ctol = s.coltol ? s.coltol[col] : tol;
+        // the convergence test first: a converged column's z is not computed
+        const bool conv = sqrt(rr) <= ctol * sqrt(bb);
+        const double rz = (XZ && conv) ? 0.0 : v[1];
+        const bool bad = !isfinite(rz) || !isfinite(rr) || !isfinite(bb);
+        if (lead && threadIdx.x == 0) {
+            if (k == 0) s.bb[col] = bb;
             s.its[col] = k;
-            s.active[cur * ncols + col] = flag == 0 ? 1 : 0;
-            if (flag == 0) s.rho[cur * ncols + col] = rz;
-            if (flag == 2) {
+            s.active[cur * ncols + col] = !bad && !conv ? 1 : 0;
+            if (!bad && !conv) s.rho[cur * ncols + col] = rz;
+            if (bad) {
                 atomicMax(&s.err[0], 7);
                 atomicMin(&s.err[1], col);
             }
         }
-    }
-    __syncthreads();
-    if (sh_flag != 0) return;
-    if constexpr (MODE == 2) {
-        struct Ep {
-            using Raw = NoRaw;
-            double acc[1];
-            __device__ static Raw zero() { return {}; }
-            __device__ Raw load(long) const { return {}; }
-            __device__ void operator()(int, long, T c, T hv, const Raw &) {
-                acc[0] += (double)c * (double)hv;
-            }
-        } ep{{0.0}};
-        LdPlain<T> l{Pnew + (long)col * ld};
-        engine<T, PPT>(g, band, zc, vs, l, ep, lds_ptr<T>());
-        block_sums<1>(ep.acc, red);
-        if (threadIdx.x == 0) s.part[3 * qs + (long)col * tiles + tile] = ep.acc[0];
-        return;
-    }
-    const T beta = (k == 0) ? T(0) : (T)(rz / s.rho[prv * ncols + col]);
+        beta = (k == 0) ? T(0) : (T)(rz / rho_old);
+        return !bad && !conv;
+    };
     EpSweep1<T> ep{Pnew + (long)col * ld, {0.0}};
+    bool run;
     if constexpr (XZ) {
-        LdPcgZ<T> l{Z + (long)col * ld, Pold + (long)col * ld, beta, k == 0};
-        engine<T, PPT>(g, band, zc, vs, l, ep, lds_ptr<T>());
+        LdPcgZ<T> l{Z + (long)col * ld, Pold + (long)col * ld, T(0), k == 0};
+        auto pre = [&] { return scalars(l.beta); };
+        run = engine<T, PPT>(g, band, zc, vs, l, ep, lds_ptr<T>(), pre);
     } else {
-        LdPcgP<T> l{dinv, R + (long)col * ld, Pold + (long)col * ld, beta, k == 0};
-        engine<T, PPT>(g, band, zc, vs, l, ep, lds_ptr<T>());
+        LdPcgP<T> l{dinv, R + (long)col * ld, Pold + (long)col * ld, T(0), k == 0};
+        auto pre = [&] { return scalars(l.beta); };
+        run = engine<T, PPT>(g, band, zc, vs, l, ep, lds_ptr<T>(), pre);
     }
+    if (!run) return;
     block_sums<1>(ep.acc, red);
     if (threadIdx.x == 0) s.part[3 * qs + (long)col * tiles + tile] = ep.acc[0];
 }
@@ -804,18 +846,18 @@ __global__ __launch_bounds__(kThreads) void k_pcg_gamma(int k, int ncols, double
         if (threadIdx.x == 0) s.active[cur * ncols + col] = 0;
         return;
     }
-    const double rr = col_sum(s.part + qs, col, tiles, red);
-    double bb;
-    if (k == 0) {
-        bb = col_sum(s.part + 2 * qs, col, tiles, red);
-        if (threadIdx.x == 0) s.bb[col] = bb;
-    } else {
-        bb = s.bb[col];
-    }
+    // all of the column's sums together: ||r||^2, ||b||^2 (k = 0), sum w z^2, gamma_old
+    const long pc = (long)col * tiles;
+    const double *const ps[4] = {s.part + qs + pc, s.part + 2 * qs + pc, wzp + (long)col * nslab,
+                                 s.part + pc};
+    const int n[4] = {tiles, k == 0 ? tiles : 0, nslab, k == 0 ? 0 : tiles};
+    double v[4];
+    dev::part_sums<4>(ps, n, v, red);
+    const double rr = v[0], bb = k == 0 ? v[1] : s.bb[col];
+    if (k == 0 && threadIdx.x == 0) s.bb[col] = bb;
     const double ctol = s.coltol ? s.coltol[col] : tol;
     const bool conv = sqrt(rr) <= ctol * sqrt(bb);
-    const double wz = conv ? 0.0 : col_sum(wzp, col, nslab, red);
-    const double gold = (conv || k == 0) ? 0.0 : col_sum(s.part, col, tiles, red);
+    const double wz = v[2], gold = v[3];
     if (threadIdx.x == 0) {
         const double rz = conv ? 0.0 : rzc[col];
         int flag = 0;  // 0 run, 1 converged, 2 non-finite
@@ -893,7 +935,6 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && !JAC && PPT == 3 ? 6 : 1)))
                                                          long ld, int ncols, int k, PcgState s,
                                                          long qs) {
     __shared__ Red red;
-    __shared__ int sh_flag;
     int col, tile, band, zc;
     tile_of(g, col, tile, band, zc);
     vs = col_pt(g, vs, col);
@@ -901,24 +942,21 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && !JAC && PPT == 3 ? 6 : 1)))
     const int cur = k & 1;
     const int tiles = g.tiles();
     if (!s.active[cur * ncols + col]) return;
-    const double gam = col_sum(s.part + 3 * qs, col, tiles, red);
-    if (threadIdx.x == 0) {
-        int flag = 0;
-        if (!isfinite(gam)) flag = 7;
-        else if (!(gam > 0.0)) flag = 5;
-        sh_flag = flag;
-        if (flag && tile == 0) {
+    const double rho = s.rho[cur * ncols + col];
+    LdPlain<T> l{Pn + (long)col * ld};
+    EpSweep2<T, JAC, XZ> ep{X + (long)col * ld, R + (long)col * ld, dinv, T(0), {0.0, 0.0}};
+    auto pre = [&] {
+        const double gam = col_sum(s.part + 3 * qs, col, tiles, red);
+        const int flag = !isfinite(gam) ? 7 : !(gam > 0.0) ? 5 : 0;
+        if (flag && tile == 0 && threadIdx.x == 0) {
             atomicMax(&s.err[0], flag);
             atomicMin(&s.err[1], col);
         }
-    }
-    __syncthreads();
-    if (sh_flag) return;
-    const T alpha = (T)(s.rho[cur * ncols + col] / gam);
-    LdPlain<T> l{Pn + (long)col * ld};
-    EpSweep2<T, JAC, XZ> ep{X + (long)col * ld, R + (long)col * ld, dinv, alpha, {0.0, 0.0}};
+        ep.alpha = (T)(rho / gam);
+        return flag == 0;
+    };
     // FP32: one prefetch set (measured faster here: the second set costs occupancy)
-    engine<T, PPT, sizeof(T) == 8>(g, band, zc, vs, l, ep, lds_ptr<T>());
+    if (!engine<T, PPT, sizeof(T) == 8>(g, band, zc, vs, l, ep, lds_ptr<T>(), pre)) return;
     block_sums<2>(ep.acc, red);
     if (threadIdx.x == 0) {
         const long o = (long)col * tiles + tile;
@@ -1146,22 +1184,17 @@ template <typename T>
 hipError_t launch_pcg_sweep1(const Grid &g, const T *vs, const T *dinv, const T *R,
                              const T *Pold, T *Pnew, long ld, int ncols, int k, double tol,
                              const int *mask, PcgState s, hipStream_t st, const float *Z,
-                             const double *rzp, int rzt, bool p_given) {
+                             const double *rzp, int rzt) {
     if (ncols <= 0) return hipSuccess;
     const long qs = (long)ncols * g.tiles();
     const dim3 grid(ncols * g.tiles());
-    if (p_given) {
-        QO_DISPATCH_PPT(g.ppt, hipLaunchKernelGGL((k_pcg_sweep1<T, P, 2>), grid,
-                                                   dim3(kThreads), lds_bytes(g, sizeof(T)), st,
-                                                   g, vs, dinv, R, Pold, Pnew, ld, ncols, k, tol,
-                                                   mask, s, qs, Z, rzp, rzt));
-    } else if (Z) {
-        QO_DISPATCH_PPT(g.ppt, hipLaunchKernelGGL((k_pcg_sweep1<T, P, 1>), grid,
+    if (Z) {
+        QO_DISPATCH_PPT(g.ppt, hipLaunchKernelGGL((k_pcg_sweep1<T, P, true>), grid,
                                                    dim3(kThreads), lds_bytes(g, sizeof(T)), st,
                                                    g, vs, dinv, R, Pold, Pnew, ld, ncols, k, tol,
                                                    mask, s, qs, Z, rzp, rzt));
     } else {
-        QO_DISPATCH_PPT(g.ppt, hipLaunchKernelGGL((k_pcg_sweep1<T, P, 0>), grid,
+        QO_DISPATCH_PPT(g.ppt, hipLaunchKernelGGL((k_pcg_sweep1<T, P, false>), grid,
                                                    dim3(kThreads), lds_bytes(g, sizeof(T)), st,
                                                    g, vs, dinv, R, Pold, Pnew, ld, ncols, k, tol,
                                                    mask, s, qs, Z, rzp, rzt));
@@ -1214,12 +1247,11 @@ template hipError_t launch_pcg_init<float>(const Grid &, const float *, const fl
 template hipError_t launch_pcg_sweep1<double>(const Grid &, const double *, const double *,
                                               const double *, const double *, double *, long,
                                               int, int, double, const int *, PcgState,
-                                              hipStream_t, const float *, const double *, int,
-                                              bool);
+                                              hipStream_t, const float *, const double *, int);
 template hipError_t launch_pcg_sweep1<float>(const Grid &, const float *, const float *,
                                              const float *, const float *, float *, long, int,
                                              int, double, const int *, PcgState, hipStream_t,
-                                             const float *, const double *, int, bool);
+                                             const float *, const double *, int);
 template hipError_t launch_pcg_sweep2<double>(const Grid &, const double *, const double *,
                                               const double *, double *, double *, long, int, int,
                                               PcgState, hipStream_t, bool, bool);
