@@ -5,6 +5,7 @@
 // hundred, so these kernels are latency-bound; the solves and the Jacobi
 // sweeps run in one workgroup with the matrices resident in L2.
 #include "qo_internal.h"
+#include "qo_device.h"
 
 namespace qo {
 
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(256) void k_gjb_update(double *__restrict__ A, int 
 // per round and nothing but the next round's angles waits for it.
 //
 // Rotation of pair i of round rnd (m players, m - 1 rounds; index n of an odd n is a dummy):
-// indices p < q, cosine and sine that zero A_pq.
+// indices p < q.
 constexpr int JT = 1024;
 
 __device__ __forceinline__ void jac_pair(int i, int rnd, int m, int &p, int &q) {
@@ -418,41 +419,83 @@ __device__ __forceinline__ void jac_pair(int i, int rnd, int m, int &p, int &q) 
     }
 }
 
-__device__ __forceinline__ void jac_rot(const double *A, int lda, int n, int p, int q, double &c,
-                                        double &s) {
-    c = 1.0;
-    s = 0.0;
-    if (q >= n) return;
-    const double apq = A[(long)q * lda + p];
-    const double app = A[(long)p * lda + p];
-    const double aqq = A[(long)q * lda + q];
-    if (apq != 0.0 && fabs(apq) > 1e-300) {
-        const double th = (aqq - app) / (2.0 * apq);
-        double t;
-        if (fabs(th) > 1e150) t = 0.5 / th;
-        else t = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-        c = 1.0 / sqrt(t * t + 1.0);
-        s = t * c;
-    }
+// 1 / sqrt(x) and 1 / x of a normal x: the hardware estimate and one step of a cubically
+// convergent iteration in its residual e (1 - x y^2, 1 - x y).
+__device__ __forceinline__ double jac_rsqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+__device__ __forceinline__ double jac_rcp(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
+// The rotation by an angle of at most 45 degrees that zeroes apq: t = tan, s = sin and
+// u = tan of half the angle (cos = 1 - s u),
+//   t = b / (d + sign(d) sqrt(d^2 + b^2)), d = aqq - app, b = 2 apq,
+// both scaled by a power of two so that the larger lies in [1/2, 1).  A round waits for this
+// chain; with library square roots and divisions it was half of the round.
+struct JacRot {
+    double t, s, u;
+};
+__device__ __forceinline__ JacRot jac_angle(double app, double aqq, double apq) {
+    if (!(fabs(apq) > 1e-300)) return {0.0, 0.0, 0.0};
+    double d = aqq - app, b = 2.0 * apq;
+    const int ex = max(__builtin_amdgcn_frexp_exp(d), __builtin_amdgcn_frexp_exp(b));
+    d = ldexp(d, -ex);
+    b = ldexp(b, -ex);
+    const double x = fma(d, d, b * b);
+    const double y = jac_rsqrt(x);
+    double h = x * y;
+    h = fma(fma(-h, h, x), 0.5 * y, h);  // sqrt(x)
+    const double v = fabs(d) + h;        // in (1/2, 3)
+    const double r = jac_rcp(v);
+    b = copysign(1.0, d) * b;
+    double t = b * r;
+    t = fma(fma(-v, t, b), r, t);
+    const double c = jac_rsqrt(fma(t, t, 1.0));
+    const double s = t * c;
+    return {t, s, s * jac_rcp(1.0 + c)};
+}
+
+// (x, y) <- (c x - s y, s x + c y) in terms of s and u: the rounding of a cosine near one,
+// which is one-sided for angles around 1e-8, does not enter (with c and s the norms of 64
+// vectors drifted by 2e-14 in nine sweeps).
+__device__ __forceinline__ void jac_turn(double s, double u, double &x, double &y) {
+    const double x0 = x;
+    x = fma(-s, fma(u, x0, y), x0);
+    y = fma(s, fma(-u, y, x0), y);
+}
+
+__device__ __forceinline__ JacRot jac_rot(const double *A, int lda, int n, int p, int q) {
+    if (q >= n) return {0.0, 0.0, 0.0};
+    return jac_angle(A[(long)p * lda + p], A[(long)q * lda + q], A[(long)q * lda + p]);
 }
 
 // Block (rows p, q; columns r, t) of A through both rotations, from A into B (may be A).  The
 // pair's own off-diagonal entry, zero up to rounding, is stored as zero: left as rounding
 // noise, the off-diagonal mass stays near 1e-32 of the total and the iteration runs all of
 // its 60 sweeps (64 x 64) instead of the eight or nine that the quadratic convergence needs.
+// The pair's diagonal entries move by t apq (one rounding; through both rotations four, and
+// the eigenvalues collect them over hundreds of rotations).
 __device__ __forceinline__ void jac_block(const double *A, int lda, double *B, int ldb, int n,
-                                          int p, int q, double ci, double si, int r, int t,
-                                          double cj, double sj) {
+                                          int p, int q, const JacRot &i, int r, int t,
+                                          const JacRot &j) {
     const bool hq = q < n, ht = t < n;  // a dummy index has no row or column
     double pr = A[(long)r * lda + p], qr = hq ? A[(long)r * lda + q] : 0.0;
     double pt = ht ? A[(long)t * lda + p] : 0.0, qt = hq && ht ? A[(long)t * lda + q] : 0.0;
-    const double pr1 = ci * pr - si * qr, qr1 = si * pr + ci * qr;
-    const double pt1 = ci * pt - si * qt, qt1 = si * pt + ci * qt;
-    pr = cj * pr1 - sj * pt1;
-    pt = sj * pr1 + cj * pt1;
-    qr = cj * qr1 - sj * qt1;
-    qt = sj * qr1 + cj * qt1;
-    if (p == r) pt = qr = 0.0;
+    if (p == r) {
+        pr = fma(-j.t, pt, pr);
+        qt = fma(j.t, pt, qt);
+        pt = qr = 0.0;
+    } else {
+        jac_turn(i.s, i.u, pr, qr);
+        jac_turn(i.s, i.u, pt, qt);
+        jac_turn(j.s, j.u, pr, pt);
+        jac_turn(j.s, j.u, qr, qt);
+    }
     B[(long)r * ldb + p] = pr;
     if (hq) B[(long)r * ldb + q] = qr;
     if (ht) B[(long)t * ldb + p] = pt;
@@ -476,59 +519,136 @@ __device__ __forceinline__ void jac_mass(const double *A, int lda, int n, double
 }
 
 // n <= kJacobiLds: A and V stay in one workgroup's LDS for the whole iteration (pitch odd:
-// a wavefront's consecutive rows fall in different banks).  A round is two barriers and
-// one LDS pass; with A and V in global memory (three barriers, every access an L2 round
-// trip) a 64 x 64 problem took 26.4 ms.
+// a wavefront's consecutive rows fall in different banks), in arrays of m rows so that the
+// dummy index needs no test: its entries are zero and its rotations the identity.  Only the
+// entries (a, b) with a <= b of A are kept.  A thread owns the block of row pair i and column
+// pair j > i in every round; its indices advance by one from round to round.  A round is
+//   A off the pairs' own entries through the round's rotations     (all wavefronts)
+//   the next round's angles and pairs' own entries | V through this round's rotations
+//                                                              (wavefront 0 | the others)
+// with a barrier after each: the angles are a serial chain on one wavefront, and V, which
+// nothing waits for, fills the others meanwhile.  A 64 x 64 problem takes 0.56 ms (about 1 us
+// per round); 26.4 ms with A and V in global memory, 0.94 ms in LDS with angles, A (both
+// triangles) and V in turn.
 constexpr int kJacobiLds = 98;
 __host__ __device__ constexpr int jac_pitch(int n) { return n | 1; }
+__host__ __device__ constexpr size_t jac_lds(int n) {
+    const int m = (n + 1) & ~1;
+    return (size_t)(2 * m * jac_pitch(m) + 2 * m) * sizeof(double);
+}
 
 __global__ __launch_bounds__(JT) void k_jacobi_lds(const double *__restrict__ Ag, int lda, int n,
-                                                   double *__restrict__ evals,
-                                                   double *__restrict__ Vg, int ldv) {
-    extern __shared__ double jsm[];
-    __shared__ double red[JT / 64];
-    const int m = (n + 1) & ~1;  // even number of players; index n is a dummy
-    const int np = m / 2, ld = jac_pitch(n);
-    double *A = jsm, *V = A + n * ld;
-    double *cs = V + n * ld;                          // [np] c
-    double *sn = cs + np;                             // [np] s
-    int *pp = reinterpret_cast<int *>(sn + np);       // [np] p
-    int *qq = pp + np;                                // [np] q
-    const int tid = threadIdx.x;
-    for (int e = tid; e < n * n; e += JT) {
-        const int c = e / n, r = e - c * n;
-        A[c * ld + r] = Ag[(long)c * lda + r];
+                                                    double *__restrict__ evals,
+                                                    double *__restrict__ Vg, int ldv) {
+    extern __shared__ __align__(16) double jsm[];
+    __shared__ double red[2][JT / 64];
+    const int m = (n + 1) & ~1;  // even number of players; index n of an odd n is a dummy
+    const int np = m / 2, ld = jac_pitch(m);
+    double2 *cs = reinterpret_cast<double2 *>(jsm);  // [2][np] s and u of each pair
+    double *A = jsm + 2 * m, *V = A + m * ld;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (int e = tid; e < m * m; e += JT) {
+        const int c = e / m, r = e - c * m;
+        A[r * ld + c] = r < n && c < n ? Ag[(long)c * lda + r] : 0.0;
         V[c * ld + r] = r == c ? 1.0 : 0.0;
+    }
+    auto at = [&](int a, int b) -> double & { return A[min(a, b) * ld + max(a, b)]; };
+    // pair i of a round: players p, q (in either order; the rotation is the same)
+    auto pair_of = [&](int i, int rnd, int &p, int &q) {
+        p = rnd + i;
+        if (p >= m - 1) p -= m - 1;
+        q = rnd - i;
+        if (q < 0) q += m - 1;
+        if (i == 0) q = m - 1;
+    };
+    auto angles = [&](int rnd, double2 *to) {  // by one wavefront: np <= 64
+        if (lane < np) {
+            int p, q;
+            pair_of(lane, rnd, p, q);
+            double *App = &at(p, p), *Aqq = &at(q, q), *Apq = &at(p, q);
+            const double app = *App, aqq = *Aqq, apq = *Apq;
+            const JacRot v = jac_angle(app, aqq, apq);
+            to[lane] = {v.s, v.u};
+            // see jac_block
+            *App = fma(-v.t, apq, app);
+            *Aqq = fma(v.t, apq, aqq);
+            *Apq = 0.0;
+        }
+    };
+    // the blocks of this thread: tid, tid + JT of the triangle i < j, column by column
+    constexpr int NB = (kJacobiLds / 2 * (kJacobiLds / 2 - 1) / 2 + JT - 1) / JT;
+    int bi[NB], bj[NB];
+#pragma unroll
+    for (int h = 0; h < NB; ++h) {
+        const int e = tid + h * JT;
+        int j = (int)((sqrtf(8.f * (float)e + 1.f) + 1.f) * 0.5f);
+        while (j * (j - 1) / 2 > e) --j;
+        while ((j + 1) * j / 2 <= e) ++j;
+        bj[h] = j;
+        bi[h] = e - j * (j - 1) / 2;
     }
     __syncthreads();
     for (int sweep = 0; sweep < 60; ++sweep) {
-        double off, tot;
-        jac_mass(A, ld, n, red, off, tot);
-        if (!(off > 1e-32 * tot)) break;  // the same in every thread
+        // squares off the diagonal and of all entries
+        double off = 0.0, dia = 0.0;
+        for (int e = tid; e < m * m; e += JT) {
+            const int a = e / m, b = e - a * m;
+            const double v = A[a * ld + b];
+            if (a < b) off = fma(v, v, off);
+            else if (a == b) dia = fma(v, v, dia);
+        }
+        off = dev::wave_sum_lane63(off);
+        dia = dev::wave_sum_lane63(dia);
+        if (lane == 63) {
+            red[0][w] = off;
+            red[1][w] = dia;
+        }
+        __syncthreads();
+        off = dia = 0.0;
+#pragma unroll
+        for (int k = 0; k < JT / 64; ++k) {
+            off += red[0][k];
+            dia += red[1][k];
+        }
+        off *= 2.0;
+        if (!(off > 1e-32 * (off + dia))) break;  // the same in every thread
+        if (w == 0) angles(0, cs);
+        __syncthreads();
         for (int rnd = 0; rnd < m - 1; ++rnd) {
-            if (tid < np) {
-                int p, q;
-                double c, s;
-                jac_pair(tid, rnd, m, p, q);
-                jac_rot(A, ld, n, p, q, c, s);
-                cs[tid] = c;
-                sn[tid] = s;
-                pp[tid] = p;
-                qq[tid] = q;
+            const double2 *cr = cs + (rnd & 1) * np;
+#pragma unroll
+            for (int h = 0; h < NB; ++h) {
+                if (bj[h] >= np) break;
+                int p, q, r, t;
+                pair_of(bi[h], rnd, p, q);
+                pair_of(bj[h], rnd, r, t);
+                const double2 ci = cr[bi[h]], cj = cr[bj[h]];
+                double *Apr = &at(p, r), *Aqr = &at(q, r), *Apt = &at(p, t), *Aqt = &at(q, t);
+                double pr = *Apr, qr = *Aqr, pt = *Apt, qt = *Aqt;
+                jac_turn(ci.x, ci.y, pr, qr);
+                jac_turn(ci.x, ci.y, pt, qt);
+                jac_turn(cj.x, cj.y, pr, pt);
+                jac_turn(cj.x, cj.y, qr, qt);
+                *Apr = pr;
+                *Aqr = qr;
+                *Apt = pt;
+                *Aqt = qt;
             }
             __syncthreads();
-            for (int e = tid; e < np * np; e += JT) {
-                const int j = e / np, i = e - j * np;
-                jac_block(A, ld, A, ld, n, pp[i], qq[i], cs[i], sn[i], pp[j], qq[j], cs[j], sn[j]);
-            }
-            for (int e = tid; e < np * n; e += JT) {
-                const int j = e / n, r = e - j * n;
-                const int p = pp[j], q = qq[j];
-                if (q >= n) continue;
-                const double c = cs[j], s = sn[j];
-                const double vp = V[p * ld + r], vq = V[q * ld + r];
-                V[p * ld + r] = c * vp - s * vq;
-                V[q * ld + r] = s * vp + c * vq;
+            if (w == 0) {
+                if (rnd + 1 < m - 1) angles(rnd + 1, cs + ((rnd + 1) & 1) * np);
+            } else {
+                for (int i = w - 1; i < np; i += JT / 64 - 1) {
+                    int p, q;
+                    pair_of(i, rnd, p, q);
+                    const double2 v = cr[i];
+                    for (int r = lane; r < n; r += 64) {
+                        double vp = V[p * ld + r], vq = V[q * ld + r];
+                        jac_turn(v.x, v.y, vp, vq);
+                        V[p * ld + r] = vp;
+                        V[q * ld + r] = vq;
+                    }
+                }
             }
             __syncthreads();
         }
@@ -548,7 +668,7 @@ __global__ __launch_bounds__(JB * JB) void k_jacobi_round(const double *__restri
                                                           double *__restrict__ B, int ldb, int n,
                                                           int rnd, double *__restrict__ V,
                                                           int ldv) {
-    __shared__ double cs[2][JB], sn[2][JB];
+    __shared__ JacRot rot[2][JB];
     __shared__ int pp[2][JB], qq[2][JB];
     const int m = (n + 1) & ~1, np = m / 2;
     const int ti = threadIdx.x & (JB - 1), tj = threadIdx.x / JB;
@@ -556,11 +676,8 @@ __global__ __launch_bounds__(JB * JB) void k_jacobi_round(const double *__restri
         const int side = threadIdx.x / JB;  // 0: row pairs, 1: column pairs
         const int i = min((int)(side ? blockIdx.y : blockIdx.x) * JB + ti, np - 1);
         int p, q;
-        double c, s;
         jac_pair(i, rnd, m, p, q);
-        jac_rot(A, lda, n, p, q, c, s);
-        cs[side][ti] = c;
-        sn[side][ti] = s;
+        rot[side][ti] = jac_rot(A, lda, n, p, q);
         pp[side][ti] = p;
         qq[side][ti] = q;
     }
@@ -568,20 +685,21 @@ __global__ __launch_bounds__(JB * JB) void k_jacobi_round(const double *__restri
     if ((int)blockIdx.y * JB + tj >= np) return;
     if (blockIdx.z == 0) {
         if ((int)blockIdx.x * JB + ti >= np) return;
-        jac_block(A, lda, B, ldb, n, pp[0][ti], qq[0][ti], cs[0][ti], sn[0][ti], pp[1][tj],
-                  qq[1][tj], cs[1][tj], sn[1][tj]);
+        jac_block(A, lda, B, ldb, n, pp[0][ti], qq[0][ti], rot[0][ti], pp[1][tj], qq[1][tj],
+                  rot[1][tj]);
         return;
     }
     const int p = pp[1][tj], q = qq[1][tj];
     if (q >= n) return;
-    const double c = cs[1][tj], s = sn[1][tj];
+    const JacRot v = rot[1][tj];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int r = (int)blockIdx.x * 2 * JB + h * JB + ti;
         if (r >= n) continue;
-        const double vp = V[(long)p * ldv + r], vq = V[(long)q * ldv + r];
-        V[(long)p * ldv + r] = c * vp - s * vq;
-        V[(long)q * ldv + r] = s * vp + c * vq;
+        double vp = V[(long)p * ldv + r], vq = V[(long)q * ldv + r];
+        jac_turn(v.s, v.u, vp, vq);
+        V[(long)p * ldv + r] = vp;
+        V[(long)q * ldv + r] = vq;
     }
 }
 
@@ -766,9 +884,8 @@ hipError_t nn_jacobi(double *A, int lda, int n, double *evals, double *V, int ld
     if (n <= 0) return hipSuccess;
     const int m = (n + 1) & ~1, np = m / 2;
     if (n <= kJacobiLds) {
-        const size_t smem = (size_t)2 * n * jac_pitch(n) * sizeof(double) +
-                            (size_t)np * (2 * sizeof(double) + 2 * sizeof(int));
-        hipLaunchKernelGGL(k_jacobi_lds, dim3(1), dim3(JT), smem, st, A, lda, n, evals, V, ldv);
+        hipLaunchKernelGGL(k_jacobi_lds, dim3(1), dim3(JT), jac_lds(n), st, A, lda, n,
+                           evals, V, ldv);
         return hipGetLastError();
     }
     // V = I; then sweeps of m - 1 rounds, the buffers swapped after each
