@@ -318,7 +318,7 @@ qo_status group_step_enqueue(qo_batch_ctx *b, qo_batch_ctx::Group &G, int par) {
     if (G.mixed) BQO(group_solve_mixed(b, G, G.Uh, Q, 1));
     else BQO(group_pcg(b, G, G.Uh, Q, 1));
     BHIP(b, launch_gram_f64_batch(G.gjob[par][1], G.ninst, G.max_gram_grid, G.ld, G.ng, G.w, st));
-    BHIP(b, launch_nn_correct(G.njob, G.ninst, st));
+    BHIP(b, launch_nn_correct(G.njob, G.ninst, G.max_n, st));
     BHIP(b, launch_tsgemm_batch(G.tjob[par][2], G.ninst, G.max_n, G.ld, G.ng, st));
     BHIP(b, launch_quad(G.g, G.vs, G.U, G.ld, G.C, G.part, st));
     BHIP(b, launch_instance_energy(G.part, G.qs, G.g.tiles(), G.coff, G.ninst, G.w, G.energy, st));

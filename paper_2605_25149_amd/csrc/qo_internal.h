@@ -326,7 +326,7 @@ int nn_slot_yr();
 int nn_slot_zr();
 int nn_slot_or();
 hipError_t launch_nn_predict(const NnJob *jobs, int njobs, int max_n, hipStream_t st);
-hipError_t launch_nn_correct(const NnJob *jobs, int njobs, hipStream_t st);
+hipError_t launch_nn_correct(const NnJob *jobs, int njobs, int max_n, hipStream_t st);
 hipError_t launch_instance_energy(const double *part, long qs, int tiles, const int *coff,
                                   int ninst, double w, double *out, hipStream_t st);
 // vs = V + sigma, dinv = 1/(c0 + vs); status = 7 (non-finite) or 5 (diagonal <= 0)

@@ -6,6 +6,7 @@
 // sweeps run in one workgroup with the matrices resident in L2.
 #include "qo_internal.h"
 #include "qo_device.h"
+#include "qo_gj.h"
 
 namespace qo {
 
@@ -159,6 +160,18 @@ __global__ __launch_bounds__(GJT) void k_gj(double *__restrict__ A, int lda,
         __syncthreads();
     }
     if (tid == 0 && fail_sh) atomicMax(status, fail_sh);
+}
+
+// n <= 64 and n + m <= 128: one launch, the matrix in registers (qo_gj.h).  Blocked, below, a
+// 32 x 32 solve took 75 us and one of 64 x 64 120; 22 and 51 here.
+template <int CPW>
+__global__ __launch_bounds__(64 * dev::kGjRegWaves) void k_gj_reg(
+    const double *__restrict__ A, int lda, double *__restrict__ B, int ldb, int n, int m, int spd,
+    int *__restrict__ status) {
+    __shared__ dev::GjShared sh;
+    if (*status) return;  // an earlier solve failed
+    const int f = dev::gj_reg<CPW>(A, lda, B, ldb, n, m, spd != 0, sh);
+    if (f && threadIdx.x == 0) atomicMax(status, f);
 }
 
 // ---- blocked Gauss-Jordan on [A | B] (n <= 512) ----------------------------
@@ -854,6 +867,18 @@ hipError_t nn_axpby(double *C, int ldc, double a, const double *A, int lda, doub
 hipError_t nn_gj_solve(double *A, int lda, double *B, int ldb, int n, int m, bool spd,
                        int *status, hipStream_t st, double *work, int *piv) {
     if (n <= 0) return hipSuccess;
+    if (n <= dev::kGjRegN && n + m <= dev::kGjRegCols) {
+        const dim3 block(64 * dev::kGjRegWaves);
+        const int cols = n + m, nw = dev::kGjRegWaves;
+#define QO_GJ_REG(CPW) \
+    hipLaunchKernelGGL(k_gj_reg<CPW>, dim3(1), block, 0, st, A, lda, B, ldb, n, m, (int)spd, status)
+        if (cols <= nw) QO_GJ_REG(1);
+        else if (cols <= 2 * nw) QO_GJ_REG(2);
+        else if (cols <= 4 * nw) QO_GJ_REG(4);
+        else QO_GJ_REG(8);
+#undef QO_GJ_REG
+        return hipGetLastError();
+    }
     if (n > kGjBlockedMax || !work || !piv) {
         const size_t smem = sizeof(double) * (size_t)(n + n + m);
         hipLaunchKernelGGL(k_gj, dim3(1), dim3(GJT), smem, st, A, lda, B, ldb, n, m, (int)spd,
