@@ -99,7 +99,7 @@ struct qo_ctx {
     _Float16 *dS = nullptr, *t1 = nullptr, *t2 = nullptr;
     float *dmu = nullptr, *pcs = nullptr;
     float *z32 = nullptr;  // preconditioned residual z = M^{-1} r (FP32 in either precision)
-    float *pbeta = nullptr;  // beta of the FP32 PCG, formed before the inverse plane pass
+    float *pbeta = nullptr;  // beta of the FP32 PCG, formed before or by the inverse plane pass
     double *rzc = nullptr;   // and r.z per column
     double *wzp = nullptr;   // partial sums of (V + sigma - vbar) z^2: per column, slab, wave
     double *rzp = nullptr, *dsum = nullptr;
@@ -400,9 +400,10 @@ qo_status precondition(qo_ctx *c, const T *R, float *Z, int ncols, int k, double
                        const int *mask, const PcgState &s) {
     hipStream_t st = c->st;
     const long qs = (long)ncols * c->g.tiles();
-    HIPC(c, launch_pc_prep(k, ncols, mask, s, qs, c->g.tiles(), tol, c->ng, c->pcs, st));
+    PcPrep prep = {false, k, ncols, c->g.tiles(), mask, s, qs, c->ng, tol, c->pcs};
+    HIPC(c, launch_pc_prep(c->dp, prep, st));
     hipEvent_t e0 = prof_begin(c);
-    HIPC(c, launch_dst_fwd<T>(c->dp, R, c->ld, ncols, c->t1, c->pcs, st));
+    HIPC(c, launch_dst_fwd<T>(c->dp, R, c->ld, ncols, c->t1, c->pcs, st, prep));
     prof_end(c, QO_KERNEL_DST_FWD, e0);
     hipEvent_t e1 = prof_begin(c);
     HIPC(c, launch_dst_pencil(c->dp, c->t1, c->t2, c->ld, ncols, c->pcs, c->rzp, st));
@@ -420,24 +421,26 @@ struct RoundPoll {
     const int *h;
 };
 
-// The FP32 form: the same passes, with beta of the PCG step taken from the pencil's r.z
-// partials before the inverse plane pass, which then writes the search direction
+// The FP32 form: the same passes, with the inverse plane pass taking beta of the PCG
+// step from the pencil's r.z partials: it writes the search direction
 // P = z + beta P_old (P = z at k = 0) instead of z, and the partial sums of w z^2 that give
 // gamma = P.H P without a pass over the grid (launch_pcg_gamma).
 qo_status precondition_p(qo_ctx *c, const float *R, const float *Pold, float *Pnew, int ncols,
                          int k, double tol, const int *mask, const PcgState &s) {
     hipStream_t st = c->st;
     const long qs = (long)ncols * c->g.tiles();
-    HIPC(c, launch_pc_prep(k, ncols, mask, s, qs, c->g.tiles(), tol, c->ng, c->pcs, st));
+    PcPrep prep = {false, k, ncols, c->g.tiles(), mask, s, qs, c->ng, tol, c->pcs};
+    HIPC(c, launch_pc_prep(c->dp, prep, st));
     hipEvent_t e0 = prof_begin(c);
-    HIPC(c, launch_dst_fwd<float>(c->dp, R, c->ld, ncols, c->t1, c->pcs, st));
+    HIPC(c, launch_dst_fwd<float>(c->dp, R, c->ld, ncols, c->t1, c->pcs, st, prep));
     prof_end(c, QO_KERNEL_DST_FWD, e0);
     hipEvent_t e1 = prof_begin(c);
     HIPC(c, launch_dst_pencil(c->dp, c->t1, c->t2, c->ld, ncols, c->pcs, c->rzp, st));
     prof_end(c, QO_KERNEL_DST_PENCIL, e1);
-    HIPC(c, launch_rho_beta(k, ncols, c->pcs, c->rzp, c->dp.rzparts, s, c->pbeta, c->rzc, st));
+    RhoBeta rb = {false, k, ncols, c->pcs, c->rzp, s.rho + ((k & 1) ^ 1) * ncols, c->rzc, c->pbeta};
+    HIPC(c, launch_rho_beta(c->dp, rb, st));
     hipEvent_t e2 = prof_begin(c);
-    HIPC(c, launch_dst_inv_p(c->dp, c->t2, k == 0 ? nullptr : Pold, c->pbeta, Pnew, c->ld, ncols,
+    HIPC(c, launch_dst_inv_p(c->dp, c->t2, k == 0 ? nullptr : Pold, rb, Pnew, c->ld, ncols,
                              c->pcs, c->vs32, c->wzp, st));
     prof_end(c, QO_KERNEL_DST_INV, e2);
     return QO_OK;

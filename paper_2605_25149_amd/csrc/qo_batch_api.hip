@@ -237,8 +237,9 @@ qo_status group_pcg(qo_batch_ctx *b, qo_batch_ctx::Group &G, const double *B, do
     const int K = G.kuse;
     for (int k = 0; k <= K; ++k) {
         if (G.dst) {
-            BHIP(b, launch_pc_prep(k, G.C, nullptr, s, G.qs, tiles, 0.0, G.ng, G.pcs, st));
-            BHIP(b, launch_dst_fwd<double>(G.dp, G.r, G.ld, G.C, G.t1, G.pcs, st));
+            PcPrep prep = {false, k, G.C, tiles, nullptr, s, G.qs, G.ng, 0.0, G.pcs};
+            BHIP(b, launch_pc_prep(G.dp, prep, st));
+            BHIP(b, launch_dst_fwd<double>(G.dp, G.r, G.ld, G.C, G.t1, G.pcs, st, prep));
             BHIP(b, launch_dst_pencil(G.dp, G.t1, G.t2, G.ld, G.C, G.pcs, G.rzp, st));
             BHIP(b, launch_dst_inv(G.dp, G.t2, G.z, G.ld, G.C, G.pcs, st));
         }
@@ -284,8 +285,9 @@ qo_status group_solve_mixed(qo_batch_ctx *b, qo_batch_ctx::Group &G, const doubl
                                        s.part, st));
         for (int k = 0; k <= K; ++k) {
             if (G.dst) {
-                BHIP(b, launch_pc_prep(k, G.C, G.mask, s, G.qs, tiles, 0.0, G.ng, G.pcs, st));
-                BHIP(b, launch_dst_fwd<float>(G.dp, G.rr32, G.ld, G.C, G.t1, G.pcs, st));
+                PcPrep prep = {false, k, G.C, tiles, G.mask, s, G.qs, G.ng, 0.0, G.pcs};
+                BHIP(b, launch_pc_prep(G.dp, prep, st));
+                BHIP(b, launch_dst_fwd<float>(G.dp, G.rr32, G.ld, G.C, G.t1, G.pcs, st, prep));
                 BHIP(b, launch_dst_pencil(G.dp, G.t1, G.t2, G.ld, G.C, G.pcs, G.rzp, st));
                 BHIP(b, launch_dst_inv(G.dp, G.t2, G.z, G.ld, G.C, G.pcs, st));
             }

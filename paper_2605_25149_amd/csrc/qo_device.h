@@ -76,6 +76,40 @@ __device__ __forceinline__ double col_sum(const double *__restrict__ part, int c
     return s[0];
 }
 
+// col_sum in three steps, for a workgroup of 128 or of 256 and more threads that has other
+// work between them: the loads of a column's partials, the wavefronts' sums into red[4],
+// and, after a barrier, the total.  Same order of additions as col_sum, so the same bits.
+struct ColParts {
+    double a, b;  // this thread's terms: as thread tid and, of 128 threads, as thread 128 + tid
+};
+__device__ __forceinline__ ColParts col_parts(const double *__restrict__ part, int tiles) {
+    auto terms = [&](int t) {
+        double s = 0.0;
+        if (t < tiles) {
+            s = part[t];
+            for (t += kThreads; t < tiles; t += kThreads) s += part[t];
+        }
+        return s;
+    };
+    const int tid = threadIdx.x;
+    return {tid < kThreads ? terms(tid) : 0.0, blockDim.x < kThreads ? terms(tid + 128) : 0.0};
+}
+__device__ __forceinline__ void col_parts_put(ColParts v, double *red) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    v.a = wave_sum_lane63(v.a);
+    if (lane == 63 && w < 4) red[w] = v.a;
+    if (blockDim.x < kThreads) {
+        v.b = wave_sum_lane63(v.b);
+        if (lane == 63) red[w + 2] = v.b;
+    }
+}
+__device__ __forceinline__ double col_parts_get(const double *red) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) s += red[w];
+    return s;
+}
+
 // Sum of lanes 0..15, in every lane (the other lanes' values do not count).
 __device__ __forceinline__ double row_sum16(double v) {
     v += dpp_move_d<0xb1>(v);

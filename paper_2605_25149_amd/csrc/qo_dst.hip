@@ -158,28 +158,53 @@ __global__ __launch_bounds__(kThreads) void k_col_scale(const double *__restrict
 
 // Per-column scale of the forward transform for PCG iteration k, 0 for the
 // columns that skip this iteration.  The activity and convergence decision is
-// the one the first PCG sweep takes (same partial sums, same reduction code),
+// the one the first PCG sweep takes (same partial sums, same order of additions),
 // so the preconditioner runs exactly on the columns that sweep then updates.
-__global__ __launch_bounds__(kThreads) void k_pc_prep(int k, int ncols, const int *__restrict__ mask,
-                                                      PcgState s, long qs, int tiles, double tol,
-                                                      long ng, float *__restrict__ pcs) {
+//
+// Up to kFusedWgs workgroups of the forward pass each of them forms the scale itself, the
+// first of a column leaving it in pcs for the passes that follow: a launch of its own
+// costs 2.7 to 4.7 us an iteration, the reduction in every workgroup 0.8 us (199^2 x 40, 280
+// workgroups) to 1.8 (61 x 75 x 52 x 37, 1924).  With 24576 (96^3 x 256) it costs 20 to 30
+// us, and the launch is kept.  The inverse pass of the FP32 PCG and its beta alike: 0.6 us at
+// 1924 workgroups and 6.5 at 24576, against 3.1 for the launch.  (Overlapped with the
+// slab's loads the reduction costs registers: 86 to 100 in the FP64 pass of 96 points, five
+// waves per SIMD to four.)
+constexpr long kFusedWgs = 4096;
+__device__ __forceinline__ float prep_scale(const PcPrep &q, int col, double *red) {
+    const bool was = q.k == 0 ? (q.mask ? q.mask[col] != 0 : true)
+                              : q.s.active[((q.k & 1) ^ 1) * q.ncols + col] != 0;
+    const dev::ColParts v = dev::col_parts(q.s.part + q.qs + (long)col * q.tiles, q.tiles);
+    if (!was) return 0.f;
+    dev::col_parts_put(v, red);
+    if (q.k == 0)
+        dev::col_parts_put(dev::col_parts(q.s.part + 2 * q.qs + (long)col * q.tiles, q.tiles),
+                           red + 4);
+    __syncthreads();
+    const double rr = dev::col_parts_get(red);
+    const double bb = q.k == 0 ? dev::col_parts_get(red + 4) : q.s.bb[col];
+    const double ctol = q.s.coltol ? q.s.coltol[col] : q.tol;
+    float sc = 0.f;
+    const bool fin = isfinite(rr) && isfinite(bb);
+    if (fin && !(sqrt(rr) <= ctol * sqrt(bb)) && rr > 0.0)
+        sc = (float)fmin(sqrt((double)q.ng / rr), kMaxColScale);
+    return __builtin_bit_cast(float,
+                              __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sc)));
+}
+
+__global__ __launch_bounds__(kThreads) void k_pc_prep(PcPrep q) {
+    __shared__ double red[8];
+    const float sc = prep_scale(q, blockIdx.x, red);
+    if (threadIdx.x == 0) q.pcs[blockIdx.x] = sc;
+}
+
+__global__ __launch_bounds__(kThreads) void k_rho_beta(RhoBeta q, int rzparts) {
     __shared__ dev::Red red;
     const int col = blockIdx.x;
-    const int prv = (k & 1) ^ 1;
-    const int prev_active = (k == 0) ? (mask ? mask[col] : 1) : s.active[prv * ncols + col];
-    if (!prev_active) {
-        if (threadIdx.x == 0) pcs[col] = 0.f;
-        return;
-    }
-    const double rr = dev::col_sum(s.part + qs, col, tiles, red);
-    const double bb = (k == 0) ? dev::col_sum(s.part + 2 * qs, col, tiles, red) : s.bb[col];
-    const double ctol = s.coltol ? s.coltol[col] : tol;
+    if (q.pcs[col] == 0.f) return;
+    const double rz = dev::col_sum(q.rzp, col, rzparts, red);
     if (threadIdx.x == 0) {
-        float sc = 0.f;
-        const bool fin = isfinite(rr) && isfinite(bb);
-        if (fin && !(sqrt(rr) <= ctol * sqrt(bb)) && rr > 0.0)
-            sc = (float)fmin(sqrt((double)ng / rr), kMaxColScale);
-        pcs[col] = sc;
+        q.rzc[col] = rz;
+        q.beta[col] = q.k == 0 ? 0.f : (float)(rz / q.rho_prev[col]);
     }
 }
 
@@ -279,24 +304,42 @@ __device__ __forceinline__ void store8(_Float16 *dst, const _Float16 *src, int l
 // PF (inverse only): store the search direction P = z + beta[c] P_old (P = z when Pold is
 // null) instead of z, and the partial sums of w z^2, w = V + sigma - vbar (vs holds
 // V + sigma per grid point), one per wave: wzp[(c * nslab + slab) * RP / 16 + wave].
+// Wavefronts per SIMD the plane pass's registers are limited to: what its forms reach by
+// themselves, give or take a register or two.
+constexpr int plane_waves(bool inv, bool big, int size, int nt) {
+    if (big || (size == 8 && nt > 6)) return 1;
+    if (!inv && nt <= 4) return 8;
+    if (size == 8) return 5;
+    return nt <= 8 ? 6 : 1;
+}
 template <typename T, bool INV, int NT, bool VEC, bool PF = false, bool BIG = false,
           bool SXB = false>
 __global__ __launch_bounds__(BIG ? 1024 : 512)
-__attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) void k_dst_plane(DstPlan p, const T *__restrict__ R,
+__attribute__((amdgpu_waves_per_eu(plane_waves(INV, BIG, (int)sizeof(T), NT)))) void k_dst_plane(DstPlan p, const T *__restrict__ R,
                                                    const _Float16 *__restrict__ Hin,
                                                    _Float16 *__restrict__ Hout,
                                                    float *__restrict__ Z, long ld,
-                                                   const float *__restrict__ pcs,
+                                                   const float *__restrict__ pcs, PcPrep prep,
                                                    const float *__restrict__ Pold = nullptr,
-                                                   const float *__restrict__ beta = nullptr,
+                                                   RhoBeta rb = {},
                                                    const float *__restrict__ vs = nullptr,
                                                    double *__restrict__ wzp = nullptr) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = xcd_remap(blockIdx.x, gridDim.x);
     int col, slab;
     plane_slab_of(L, p.nslab, col, slab);
-    const float sc = pcs[col];
+    __shared__ double red[INV ? (PF ? 4 : 1) : 8];
+    float sc;
+    if (!INV && prep.fused) {
+        sc = prep_scale(prep, col, red);
+        if (slab == 0 && threadIdx.x == 0) prep.pcs[col] = sc;
+    } else {
+        sc = pcs[col];
+    }
     if (sc == 0.f) return;  // column converged or inactive (uniform over the block)
+    dev::ColParts rzv = {};
+    if constexpr (PF)
+        if (rb.fused) rzv = dev::col_parts(rb.rzp + (long)col * p.rzparts, p.rzparts);
 
     constexpr int NXP = 16 * NT, XP = NXP + 8;  // the launch dispatches NT = NXP / 16
     const int nx = p.nx;
@@ -375,6 +418,7 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
         SxL = dstS;  // the staging barrier below also covers this copy
     }
 
+    if (PF && rb.fused) dev::col_parts_put(rzv, red);  // read behind the barriers below
     if constexpr (!INV) {
 #pragma unroll
         for (int q = 0; q < QF; ++q) {
@@ -480,7 +524,16 @@ __attribute__((amdgpu_waves_per_eu(!BIG && sizeof(T) == 4 && NT <= 8 ? 6 : 1))) 
             (float)(1.0 / ((double)sc * (double)(p.clmin ? p.clmin[col] : p.lmin)));
         const int g4 = NXP / 4;
         const bool first = !PF || Pold == nullptr;
-        const float b = first ? 0.f : beta[col];
+        float b = 0.f;
+        if constexpr (PF) {
+            if (rb.fused) {
+                const double rz = dev::col_parts_get(red);
+                if (slab == 0 && tid == 0) rb.rzc[col] = rz;
+                if (!first) b = (float)(rz / rb.rho_prev[col]);
+            } else if (!first) {
+                b = rb.beta[col];
+            }
+        }
         float vb = 0.f;
         if constexpr (PF) vb = p.cvbar ? p.cvbar[col] : p.vbar;
         const long pbase = base - (long)col * ld;  // the slab's offset within a column
@@ -561,9 +614,9 @@ __global__ __launch_bounds__(256) void k_dst_rows(DstPlan p, const T *__restrict
                                                   const _Float16 *__restrict__ Hin,
                                                   _Float16 *__restrict__ Hout,
                                                   float *__restrict__ Z, long ld,
-                                                  const float *__restrict__ pcs,
+                                                  const float *__restrict__ pcs, PcPrep prep,
                                                   const float *__restrict__ Pold = nullptr,
-                                                  const float *__restrict__ beta = nullptr,
+                                                  RhoBeta rb = {},
                                                   const float *__restrict__ vs = nullptr,
                                                   double *__restrict__ wzp = nullptr) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -571,8 +624,18 @@ __global__ __launch_bounds__(256) void k_dst_rows(DstPlan p, const T *__restrict
     const int L = xcd_remap(blockIdx.x, gridDim.x);
     int col, slab;
     plane_slab_of(L, p.nslab, col, slab);
-    const float sc = pcs[col];
+    __shared__ double red[INV ? (PF ? 4 : 1) : 8];
+    float sc;
+    if (!INV && prep.fused) {
+        sc = prep_scale(prep, col, red);
+        if (slab == 0 && threadIdx.x == 0) prep.pcs[col] = sc;
+    } else {
+        sc = pcs[col];
+    }
     if (sc == 0.f) return;  // column converged or inactive (uniform over the block)
+    dev::ColParts rzv = {};
+    if constexpr (PF)
+        if (rb.fused) rzv = dev::col_parts(rb.rzp + (long)col * p.rzparts, p.rzparts);
     const int nx = p.nx, row0 = slab * kRowSlab;
     const int rows = min(kRowSlab, p.ny - row0);
     const long base = (long)col * ld + (long)row0 * nx;
@@ -607,6 +670,7 @@ __global__ __launch_bounds__(256) void k_dst_rows(DstPlan p, const T *__restrict
             *reinterpret_cast<v4h *>(X + r * XP + x) = h;
         }
     } else {
+        if (PF && rb.fused) dev::col_parts_put(rzv, red);  // read behind the barriers below
         constexpr int QI = (NT + 3) / 4;  // groups of 8 per thread
         v8h hv[QI];
         bool ok[QI];
@@ -665,7 +729,16 @@ __global__ __launch_bounds__(256) void k_dst_rows(DstPlan p, const T *__restrict
         const float unscale =
             (float)(1.0 / ((double)sc * (double)(p.clmin ? p.clmin[col] : p.lmin)));
         const bool first = !PF || Pold == nullptr;
-        const float b = first ? 0.f : beta[col];
+        float b = 0.f;
+        if constexpr (PF) {
+            if (rb.fused) {
+                const double rz = dev::col_parts_get(red);
+                if (slab == 0 && tid == 0) rb.rzc[col] = rz;
+                if (!first) b = (float)(rz / rb.rho_prev[col]);
+            } else if (!first) {
+                b = rb.beta[col];
+            }
+        }
         float vb = 0.f;
         if constexpr (PF) vb = p.cvbar ? p.cvbar[col] : p.vbar;
         const long pbase = (long)row0 * nx;
@@ -1117,11 +1190,20 @@ hipError_t launch_col_scale(const double *R, long ld, long ng, int ncols, float 
     return hipGetLastError();
 }
 
-hipError_t launch_pc_prep(int k, int ncols, const int *mask, PcgState s, long qs, int tiles,
-                          double tol, long ng, float *pcs, hipStream_t st) {
-    if (ncols <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pc_prep, dim3(ncols), dim3(kThreads), 0, st, k, ncols, mask, s, qs,
-                       tiles, tol, ng, pcs);
+bool dst_prep_fused(const DstPlan &p, int ncols) { return (long)ncols * p.nslab <= kFusedWgs; }
+
+hipError_t launch_pc_prep(const DstPlan &p, PcPrep &prep, hipStream_t st) {
+    if (prep.ncols <= 0) return hipSuccess;
+    prep.fused = dst_prep_fused(p, prep.ncols);
+    if (!prep.fused) hipLaunchKernelGGL(k_pc_prep, dim3(prep.ncols), dim3(kThreads), 0, st, prep);
+    return hipGetLastError();
+}
+
+hipError_t launch_rho_beta(const DstPlan &p, RhoBeta &rb, hipStream_t st) {
+    if (rb.ncols <= 0) return hipSuccess;
+    rb.fused = dst_prep_fused(p, rb.ncols);
+    if (!rb.fused)
+        hipLaunchKernelGGL(k_rho_beta, dim3(rb.ncols), dim3(kThreads), 0, st, rb, p.rzparts);
     return hipGetLastError();
 }
 
@@ -1180,10 +1262,11 @@ static hipError_t launch_plane(const DstPlan &p, int ncols, size_t lds, hipStrea
 
 template <typename T>
 hipError_t launch_dst_fwd(const DstPlan &p, const T *R, long ld, int ncols, _Float16 *t1,
-                          const float *pcs, hipStream_t st) {
+                          const float *pcs, hipStream_t st, const PcPrep &prep) {
     if (ncols <= 0) return hipSuccess;
     return launch_plane<T, false, false>(p, ncols, dst_plane_lds(p, false), st, R,
-                                         (const _Float16 *)nullptr, t1, (float *)nullptr, ld, pcs);
+                                         (const _Float16 *)nullptr, t1, (float *)nullptr, ld, pcs,
+                                         prep);
 }
 
 // Persistent grid: as many workgroups as are resident at once (the runtime's occupancy for
@@ -1242,27 +1325,10 @@ hipError_t launch_dst_inv(const DstPlan &p, const _Float16 *t2, float *Z, long l
     if (ncols <= 0) return hipSuccess;
     return launch_plane<float, true, false>(p, ncols, dst_plane_lds(p, true), st,
                                             (const float *)nullptr, t2, (_Float16 *)nullptr, Z, ld,
-                                            pcs);
+                                            pcs, PcPrep{});
 }
 
 namespace {
-// rzc[c] = rho_k = r.z from the pencil's partials (the first sweep takes it from here) and
-// beta[c] = rho_k / rho_{k-1}, 0 at k = 0; columns with pcs[c] == 0 skipped.
-__global__ __launch_bounds__(kThreads) void k_rho_beta(int k, int ncols,
-                                                       const float *__restrict__ pcs,
-                                                       const double *__restrict__ rzp, int rzt,
-                                                       PcgState s, float *__restrict__ beta,
-                                                       double *__restrict__ rzc) {
-    __shared__ dev::Red red;
-    const int col = blockIdx.x;
-    if (pcs[col] == 0.f) return;
-    const double rz = dev::col_sum(rzp, col, rzt, red);
-    if (threadIdx.x == 0) {
-        rzc[col] = rz;
-        beta[col] = k == 0 ? 0.f : (float)(rz / s.rho[((k & 1) ^ 1) * ncols + col]);
-    }
-}
-
 // Z (FP64) = Z32 for columns with pcs[c] != 0, else 0.
 __global__ void k_z_expand(const float *__restrict__ Z32, const float *__restrict__ pcs,
                            double *__restrict__ Z, long ld, long ng) {
@@ -1274,21 +1340,13 @@ __global__ void k_z_expand(const float *__restrict__ Z32, const float *__restric
 }
 }  // namespace
 
-hipError_t launch_rho_beta(int k, int ncols, const float *pcs, const double *rzp, int rzt,
-                           PcgState s, float *beta, double *rzc, hipStream_t st) {
-    if (ncols <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_rho_beta, dim3(ncols), dim3(kThreads), 0, st, k, ncols, pcs, rzp, rzt, s,
-                       beta, rzc);
-    return hipGetLastError();
-}
-
 hipError_t launch_dst_inv_p(const DstPlan &p, const _Float16 *t2, const float *Pold,
-                            const float *beta, float *P, long ld, int ncols, const float *pcs,
+                            const RhoBeta &rb, float *P, long ld, int ncols, const float *pcs,
                             const float *vs, double *wzp, hipStream_t st) {
     if (ncols <= 0) return hipSuccess;
     return launch_plane<float, true, true>(p, ncols, dst_plane_lds(p, true), st,
                                            (const float *)nullptr, t2, (_Float16 *)nullptr, P, ld,
-                                           pcs, Pold, beta, vs, wzp);
+                                           pcs, PcPrep{}, Pold, rb, vs, wzp);
 }
 
 hipError_t launch_z_expand(const float *Z32, const float *pcs, double *Z, long ld, long ng,
@@ -1302,8 +1360,8 @@ hipError_t launch_z_expand(const float *Z32, const float *pcs, double *Z, long l
 }
 
 template hipError_t launch_dst_fwd<double>(const DstPlan &, const double *, long, int,
-                                           _Float16 *, const float *, hipStream_t);
+                                           _Float16 *, const float *, hipStream_t, const PcPrep &);
 template hipError_t launch_dst_fwd<float>(const DstPlan &, const float *, long, int, _Float16 *,
-                                          const float *, hipStream_t);
+                                          const float *, hipStream_t, const PcPrep &);
 
 }  // namespace qo

@@ -136,9 +136,32 @@ hipError_t launch_sum(const double *v, long n, double *out, hipStream_t st);
 // pcs[c] = sqrt(Ng / ||r_c||^2) (0 for a zero column)
 hipError_t launch_col_scale(const double *R, long ld, long ng, int ncols, float *pcs,
                             hipStream_t st);
-// pcs[c] = sqrt(Ng / ||r_c||^2) for the columns the PCG iteration k updates, else 0
-hipError_t launch_pc_prep(int k, int ncols, const int *mask, PcgState s, long qs, int tiles,
-                          double tol, long ng, float *pcs, hipStream_t st);
+// PCG iteration k's scales pcs[c] = sqrt(Ng / ||r_c||^2) for the columns it updates, else 0,
+// from the partial sums of ||r||^2.  launch_pc_prep forms them where that is a launch of its
+// own and clears `fused`; else the forward pass does (dst_prep_fused).
+struct PcPrep {
+    bool fused;
+    int k, ncols, tiles;
+    const int *mask;
+    PcgState s;
+    long qs, ng;
+    double tol;
+    float *pcs;
+};
+bool dst_prep_fused(const DstPlan &p, int ncols);
+hipError_t launch_pc_prep(const DstPlan &p, PcPrep &prep, hipStream_t st);
+// FP32 PCG with the fast-Poisson preconditioner, iteration k: rzc[c] = rho_k = r.z from the
+// pencil's partials and beta[c] = rho_k / rho_{k-1} (0 at k = 0) for the preconditioned
+// columns, by a launch of its own or, likewise, by the inverse pass that needs beta.
+struct RhoBeta {
+    bool fused;
+    int k, ncols;
+    const float *pcs;
+    const double *rzp, *rho_prev;
+    double *rzc;
+    float *beta;
+};
+hipError_t launch_rho_beta(const DstPlan &p, RhoBeta &rb, hipStream_t st);
 // z = M^{-1} r in three passes: forward plane (r -> t1), pencil (t1 -> t2, and the
 // partials rzp[c * rzparts + i] of r.z, summed in the spectral domain), inverse plane
 // (t2 -> z).
@@ -146,21 +169,17 @@ hipError_t launch_pc_prep(int k, int ncols, const int *mask, PcgState s, long qs
 // are not used): see kSlack.
 template <typename T>
 hipError_t launch_dst_fwd(const DstPlan &p, const T *R, long ld, int ncols, _Float16 *t1,
-                          const float *pcs, hipStream_t st);
+                          const float *pcs, hipStream_t st, const PcPrep &prep = {});
 hipError_t launch_dst_pencil(const DstPlan &p, const _Float16 *t1, _Float16 *t2, long ld,
                              int ncols, const float *pcs, double *rzp, hipStream_t st);
 // z is FP32 in either precision (its values carry FP32 precision); launch_z_expand gives
 // an FP64 copy.
 hipError_t launch_dst_inv(const DstPlan &p, const _Float16 *t2, float *Z, long ld, int ncols,
                           const float *pcs, hipStream_t st);
-// FP32 PCG with the fast-Poisson preconditioner, iteration k: rzc[c] = rho_k = r.z from the
-// pencil's partials and beta[c] = rho_k / rho_{k-1} (0 at k = 0) for the preconditioned
-// columns; then the inverse plane pass forms the search direction P = z + beta P_old
-// itself (P = z when Pold is null), and the first sweep takes rho_k from rzc.
-hipError_t launch_rho_beta(int k, int ncols, const float *pcs, const double *rzp, int rzt,
-                           PcgState s, float *beta, double *rzc, hipStream_t st);
+// The inverse plane pass of the FP32 PCG forms the search direction P = z + beta P_old
+// itself (P = z when Pold is null).
 hipError_t launch_dst_inv_p(const DstPlan &p, const _Float16 *t2, const float *Pold,
-                            const float *beta, float *P, long ld, int ncols, const float *pcs,
+                            const RhoBeta &rb, float *P, long ld, int ncols, const float *pcs,
                             const float *vs, double *wzp, hipStream_t st);
 // ... and, with the inverse pass's partials wzp of sum (V + sigma - vbar) z^2 (nwz per
 // column), the first

@@ -46,3 +46,25 @@ def test_precond_edges(oracle_mod, n):
         rel = np.linalg.norm(res, axis=0) / np.linalg.norm(R, axis=0)
         assert np.all(rel <= 2e-10), (precision, rel)
         assert np.all(it <= 40), (precision, it)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,slabs", [((20, 18, 16), 16), ((24, 50, 16), 16), ((21, 100, 16), 16),
+                                     ((20, 140, 16), 16), ((33, 256), 8)],
+                         ids=lambda n: "x".join(map(str, n)) if isinstance(n, tuple) else "")
+def test_fused_scalars_bitwise(n, slabs, precision):
+    """Up to 4096 workgroups the plane passes form the scales and beta themselves, with one
+    column more launches of their own do, adding in the same order: the columns of both
+    solves are the same bits."""
+    from paper_2605_25149_amd import binding as B
+
+    C = 4096 // slabs
+    V = inputs.gaussian_wells(n, seed=2) + 25.0
+    R = B.as_block(inputs.random_block(int(np.prod(n)), C + 1, seed=7))
+    with B.Solver(len(n), n, C + 1, precond="fast_poisson", precision=precision,
+                  pcg_tol=1e-10) as s:
+        s.set_potential(V)
+        X0, it0 = s.solve(R[:C])
+        X1, it1 = s.solve(R)
+        assert np.array_equal(it0, it1[:C])
+        assert np.array_equal(B.to_numpy(X0), B.to_numpy(X1)[:, :C])
