@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kThreads) void k_col_scale(const double *__restrict
 //
 // Up to kFusedWgs workgroups of the forward pass each of them forms the scale itself, the
 // first of a column leaving it in pcs for the passes that follow: a launch of its own
-// costs 2.7 to 4.7 us an iteration, the reduction in every workgroup 0.8 us (199^2 x 40, 280
+// costs 2.7 to 4.7 us an iteration, the reduction in every workgroup 0.8 us (199^2 x 15, 105
 // workgroups) to 1.8 (61 x 75 x 52 x 37, 1924).  With 24576 (96^3 x 256) it costs 20 to 30
 // us, and the launch is kept.  The inverse pass of the FP32 PCG and its beta alike: 0.6 us at
 // 1924 workgroups and 6.5 at 24576, against 3.1 for the launch.  (Overlapped with the
@@ -285,6 +285,16 @@ __device__ __forceinline__ void store8(_Float16 *dst, const _Float16 *src, int l
     }
 }
 
+// Wavefronts per SIMD the plane pass's registers are limited to: what its forms reach by
+// themselves, give or take a register or two (FP64 forward, 96 points: 100 registers and four
+// waves without the limit, 83 and five with it).
+constexpr int plane_waves(bool inv, bool big, int size, int nt) {
+    if (big || (size == 8 && nt > 6)) return 1;
+    if (!inv && nt <= 4) return 8;
+    if (size == 8) return 5;
+    return nt <= 8 ? 6 : 1;
+}
+
 // ---------------------------------------------------------------- plane pass
 //
 // 3-D.  Workgroup = one z-plane of one column: RP = 16 * waves padded rows of NXP
@@ -295,8 +305,8 @@ __device__ __forceinline__ void store8(_Float16 *dst, const _Float16 *src, int l
 // VEC: rows are whole 16-byte groups (nx % 8 == 0).  Otherwise the last group of a row is
 // loaded past the row's end (every array has some values of slack after its last one) and
 // masked, and stored value by value.
-// FP32 3-D planes (NT <= 8) are held to 80 registers: 6 waves per SIMD, four 6-wave
-// workgroups per CU, as many as their LDS allows.
+// FP32 3-D planes (NT <= 8) are held to at most 80 registers (plane_waves): 6 waves per SIMD,
+// four 6-wave workgroups per CU, as many as their LDS allows.
 // BIG (3-D planes of more than 128 padded rows, up to 256): up to 16 waves per workgroup,
 // S_y fragments for up to 256 rows, and the inverse pass stages its FP32 output in two
 // halves of the rows (the whole slab in FP32 would not fit the LDS).  SXB: the BIG form
@@ -304,14 +314,6 @@ __device__ __forceinline__ void store8(_Float16 *dst, const _Float16 *src, int l
 // PF (inverse only): store the search direction P = z + beta[c] P_old (P = z when Pold is
 // null) instead of z, and the partial sums of w z^2, w = V + sigma - vbar (vs holds
 // V + sigma per grid point), one per wave: wzp[(c * nslab + slab) * RP / 16 + wave].
-// Wavefronts per SIMD the plane pass's registers are limited to: what its forms reach by
-// themselves, give or take a register or two.
-constexpr int plane_waves(bool inv, bool big, int size, int nt) {
-    if (big || (size == 8 && nt > 6)) return 1;
-    if (!inv && nt <= 4) return 8;
-    if (size == 8) return 5;
-    return nt <= 8 ? 6 : 1;
-}
 template <typename T, bool INV, int NT, bool VEC, bool PF = false, bool BIG = false,
           bool SXB = false>
 __global__ __launch_bounds__(BIG ? 1024 : 512)
