@@ -448,15 +448,17 @@ __device__ __forceinline__ double jac_rcp(double x) {
 // The rotation by an angle of at most 45 degrees that zeroes apq: t = tan, s = sin and
 // u = tan of half the angle (cos = 1 - s u),
 //   t = b / (d + sign(d) sqrt(d^2 + b^2)), d = aqq - app, b = 2 apq,
-// both scaled by a power of two so that the larger lies in [1/2, 1).  A round waits for this
-// chain; with library square roots and divisions it was half of the round.
+// both scaled by a power of two so that the larger lies in [1/2, 1): the exponent is that of
+// the larger magnitude, never that of a zero d, which is 0 and would leave a small b to
+// underflow when squared.  A round waits for this chain; with library square roots and
+// divisions it was half of the round.
 struct JacRot {
     double t, s, u;
 };
 __device__ __forceinline__ JacRot jac_angle(double app, double aqq, double apq) {
     if (!(fabs(apq) > 1e-300)) return {0.0, 0.0, 0.0};
     double d = aqq - app, b = 2.0 * apq;
-    const int ex = max(__builtin_amdgcn_frexp_exp(d), __builtin_amdgcn_frexp_exp(b));
+    const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(b)));
     d = ldexp(d, -ex);
     b = ldexp(b, -ex);
     const double x = fma(d, d, b * b);
