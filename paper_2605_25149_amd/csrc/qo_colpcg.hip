@@ -273,6 +273,15 @@ __device__ __forceinline__ double obs(const double *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// This wavefront's published values have arrived, and what follows stays behind them.  The
+// builtin touches no memory in the compiler's model, so without the two compiler barriers a
+// relaxed store or the counter's addition could be moved across it.
+__device__ __forceinline__ void published() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+}
+
 struct CluSync {
     int *abort, *ctr;    // this cluster's counter
     double *slots;       // [2][3][kCluMaxW]: parity, value, workgroup
@@ -291,7 +300,7 @@ __device__ __forceinline__ bool clu_sums(double (&v)[NQ], CluSync &c, double (*s
     if (lane == 63)
 #pragma unroll
         for (int q = 0; q < NQ; ++q) sh[q][wid] = v[q];
-    __builtin_amdgcn_s_waitcnt(0);  // this wavefront's published values have arrived
+    published();
     __syncthreads();
     if (wid == 0) {
         ++c.epoch;
@@ -303,8 +312,7 @@ __device__ __forceinline__ bool clu_sums(double (&v)[NQ], CluSync &c, double (*s
         if (lane == 0) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) pub(slot + q * kCluMaxW + c.w, t[q]);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_s_waitcnt(0);
+            published();
             __hip_atomic_fetch_add(c.ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const int target = c.epoch * c.W;
             int n = 0;
