@@ -273,13 +273,11 @@ __device__ __forceinline__ double obs(const double *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// This wavefront's published values have arrived, and what follows stays behind them.  The
-// builtin touches no memory in the compiler's model, so without the two compiler barriers a
-// relaxed store or the counter's addition could be moved across it.
+// This wavefront's published values have arrived, and no store before is moved behind: the
+// wait alone touches no memory in the compiler's model, and a relaxed store could sink below.
 __device__ __forceinline__ void published() {
-    asm volatile("" ::: "memory");
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);
-    asm volatile("" ::: "memory");
 }
 
 struct CluSync {
