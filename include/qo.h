@@ -321,7 +321,10 @@ const char *qo_batch_last_error(qo_batch b);
  * regular one and counts 0.8 of a column-iteration.  QO_KERNEL_RESID covers the FP64
  * residual passes of QO_MIXED, the ones that also apply the previous round's correction
  * x + d included.  An FP64 Jacobi solve on a grid small enough to keep its columns on the
- * chip (up to 524288 points) is a QO_KERNEL_CG_F64 launch or a few instead of sweeps. */
+ * chip (up to 524288 points) is a QO_KERNEL_CG_F64 launch or a few instead of sweeps; above
+ * 8192 points its workgroups wait for one another, and if another process or a kernel that
+ * waits keeps some of them off the GPU for about a second, the handle says so on stderr and
+ * takes a form without such waits from then on. */
 typedef enum {
     QO_KERNEL_SWEEP1_F64 = 0, QO_KERNEL_SWEEP2_F64 = 1, QO_KERNEL_SWEEP1_F32 = 2,
     QO_KERNEL_SWEEP2_F32 = 3, QO_KERNEL_GRAM = 4, QO_KERNEL_UPDATE = 5, QO_KERNEL_RESID = 6,

@@ -93,6 +93,7 @@ struct qo_ctx {
     int *cluctl = nullptr;
     double *cluslot = nullptr;
     int colchunk = 8192;  // iterations per launch of that form
+    bool clugiveup = false;
     // fast-Poisson preconditioner (precond == 1)
     bool dst = false;
     DstPlan dp{};
@@ -450,7 +451,8 @@ qo_status precondition_p(qo_ctx *c, const float *R, const float *Pold, float *Pn
 // (launch_pcg_cluster) per column: one launch for the whole solve, continued every colchunk
 // iterations so that no launch runs unboundedly long when pcg_maxit is large (and cut into
 // ranges of columns, eight per cluster).  Counts and states are written straight to pinned
-// host memory.  *stalled: a cluster's wait ran out (nothing else is reported then).
+// host memory.  *stalled: a cluster's wait ran out; nothing else is reported then, and each
+// column of X holds its solution, an iterate, what it held before, or parts of these.
 qo_status pcg_onchip(qo_ctx *c, const double *B, double *X, int ncols, int use_x0, double tol,
                      int *its_out, const char *what, bool *stalled) {
     hipStream_t st = c->st;
@@ -472,7 +474,7 @@ qo_status pcg_onchip(qo_ctx *c, const double *B, double *X, int ncols, int use_x
                 HIPC(c, launch_pcg_cluster(c->g, c->nclus, c->vs, c->dinv, B, X, c->r, c->pa, c->pb,
                                            c->ld, c0, std::min(ncols, c0 + range), use_x0, tol, k0,
                                            kend, last, c->part, its, state, c->cluctl, c->cluslot,
-                                           st));
+                                           c->clugiveup, st));
             else
                 HIPC(c, launch_pcg_column(c->g, c->vs, c->dinv, B, X, c->r, c->pa, c->ld, ncols,
                                           use_x0, tol, k0, kend, last, c->part, its, state, st));
@@ -539,13 +541,18 @@ qo_status pcg(qo_ctx *c, const T *vs, const T *dinv, const T *B, T *X, T *R, T *
               const RoundPoll *outer = nullptr, bool *outer_done = nullptr,
               int *its_async = nullptr) {
     if constexpr (sizeof(T) == 8)
-        if (c->colpcg) {
+        while (c->colpcg) {
             bool stalled = false;
             const qo_status s_ = pcg_onchip(c, B, X, ncols, use_x0, tol, its_out, what, &stalled);
             if (!stalled) return s_;
-            // the streaming sweeps from what X holds, for good (the workspace they need is
-            // there in any case)
-            c->colpcg = false;
+            // Solved anew by the form without a wait, from zero or (use_x0) from what X holds,
+            // and so are the handle's later solves: each would wait in vain as long
+            c->nclus = 0;
+            c->colpcg = pcg_column_fits(c->g);
+            fprintf(stderr,
+                    "libqo_hip: the workgroups of a solve were not resident together (something "
+                    "else holds part of the GPU); this handle's solves take %s from now on\n",
+                    c->colpcg ? "one workgroup per column" : "the streaming sweeps");
         }
     const Grid &g = c->g;
     hipStream_t st = c->st;
@@ -1722,6 +1729,7 @@ qo_status qo_create(const qo_config *cfg, void *hip_stream, qo_handle *out) {
         }
     }
     h->colchunk = std::max(1, env_int("QO_COL_CHUNK", h->colchunk));
+    h->clugiveup = env_int("QO_CLU_GIVE_UP", 0) != 0;
     A(&h->nact, 1);
     A(&h->dstatus, 1);
     if (c.precond == 1) {

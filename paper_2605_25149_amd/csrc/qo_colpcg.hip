@@ -252,13 +252,15 @@ __global__ __launch_bounds__(NT) void k_pcg_column(Grid g, const double *__restr
 // (eight columns at a time), 70 x 70 x 80 x 64 163 -> 65 ms, 40^3 x 64 24.0 -> 4.9 ms, 199^2 x
 // 64 48.4 -> 12.3 ms, 256^2 x 256 332 -> 62.9 ms, 64^3 x 4 21.3 -> 4.1 ms.
 //
-// All workgroups of a launch have to be resident at once: there are at most as many as CUs,
-// each CU holds at least one, other kernels end by themselves, and two such launches never
-// meet on a device (each waits for the event of the one before it).  Every wait is bounded
-// all the same, and a workgroup that runs out of polls raises `abort`, on which all of them
-// leave and the host takes the streaming sweeps.  A cooperative launch would guarantee as
-// much, but after the first one of a process its streams overlap less: 16 grouped problems
-// on four streams stepped in 86 ms instead of 70 from then on.
+// All workgroups of a launch have to be resident at once.  Within a process they are: there are
+// at most as many as CUs, each CU holds at least one, other kernels end by themselves, and
+// two such launches never meet on a device (each waits for the event of the one before it).
+// Another process on the GPU, or a kernel that itself waits for something, can hold CUs for
+// longer.  So every wait is bounded: a workgroup that runs out of polls raises `abort`, on
+// which all of them leave, and the host takes another form for the rest of the handle's life.
+// A cooperative launch would ensure no more, and after the first one of a process its streams
+// overlap less: 16 grouped problems on four streams stepped in 86 ms instead of 70 from then
+// on.
 constexpr int kCluThreads = 512;
 constexpr int kCluPts = 8192;      // 512 threads x 16 (1024 x 8 spills some 80 registers)
 constexpr int kCluMaxW = 64;       // one partial per lane of a wavefront
@@ -641,12 +643,13 @@ hipError_t launch_pcg_cluster(const Grid &g, int nclus, const double *vs, const 
                               const double *B, double *X, double *Zx, double *R, double *P, long ld,
                               int c0, int c1, int use_x0, double tol, int k0, int kend, bool last,
                               double *scal, int *its, int *state, int *ctl, double *slots,
-                              hipStream_t st) {
+                              bool give_up, hipStream_t st) {
     if (c1 <= c0) return hipSuccess;
     CluShape sh = clu_shape(g);
     if (sh.W == 0 || g.cinst || nclus < 1 || nclus > kCluMaxClusters) return hipErrorInvalidValue;
     nclus = std::min(nclus, c1 - c0);
-    hipError_t e = launch_fill_int(ctl, (int)pcg_cluster_ints(), 0, st);
+    // give_up: counters that no wait sees completed, and the abort flag raised
+    hipError_t e = launch_fill_int(ctl, (int)pcg_cluster_ints(), give_up ? -(1 << 30) : 0, st);
     if (e != hipSuccess) return e;
     // one at a time per device (see above): each launch waits for the one before it, on
     // whichever stream and handle that was

@@ -239,7 +239,7 @@ hipError_t launch_pcg_column(const Grid &g, const double *vs, const double *dinv
 // take this form), pcg_cluster_count(g) clusters resident at a time (0: not available).  Takes
 // columns c0 .. c1 - 1; Zx, R, P: blocks; ctl: pcg_cluster_ints() ints, ctl[0] != 0 after
 // the launch: the wait for the other workgroups ran out and the results do not hold; slots:
-// pcg_cluster_slots() doubles.
+// pcg_cluster_slots() doubles.  give_up: every wait runs out (for tests of what follows).
 constexpr int kCluMaxClusters = 128;
 int pcg_cluster_width(const Grid &g);
 int pcg_cluster_count(const Grid &g);
@@ -249,7 +249,7 @@ hipError_t launch_pcg_cluster(const Grid &g, int nclus, const double *vs, const 
                               const double *B, double *X, double *Zx, double *R, double *P, long ld,
                               int c0, int c1, int use_x0, double tol, int k0, int kend, bool last,
                               double *scal, int *its, int *state, int *ctl, double *slots,
-                              hipStream_t st);
+                              bool give_up, hipStream_t st);
 
 // One-reduction (Chronopoulos-Gear) PCG: delta0 = u.Hu with u = D r0 into
 // part[3] (after launch_pcg_init on the same grid), then one sweep per iteration.
