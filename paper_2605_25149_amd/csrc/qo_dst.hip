@@ -285,14 +285,17 @@ __device__ __forceinline__ void store8(_Float16 *dst, const _Float16 *src, int l
     }
 }
 
-// Wavefronts per SIMD the plane pass's registers are limited to: what its forms reach by
-// themselves, give or take a register or two (FP64 forward, 96 points: 100 registers and four
-// waves without the limit, 83 and five with it).
+// Wavefronts per SIMD the plane pass's registers are limited to (1: no limit beyond the
+// workgroup's size).  Up to 128 points it is what the forms reach by themselves, give or take
+// a register or two (FP64 forward, 96 points: 100 registers and four waves without the limit, 83
+// and five with it).  Wider forward forms are held to four, which is two 8-wave workgroups per
+// CU (256 x 128 x 80, 56 columns: FP32 249 -> 195 us, FP64 431 -> 395); wider inverse forms
+// lose more to spills than the second workgroup gives (289 -> 309 us with the limit).
 constexpr int plane_waves(bool inv, bool big, int size, int nt) {
-    if (big || (size == 8 && nt > 6)) return 1;
+    if (big || (inv && nt > 8)) return 1;
+    if (nt > 8 || (size == 8 && nt > 6)) return 4;
     if (!inv && nt <= 4) return 8;
-    if (size == 8) return 5;
-    return nt <= 8 ? 6 : 1;
+    return size == 8 ? 5 : 6;
 }
 
 // ---------------------------------------------------------------- plane pass
@@ -380,18 +383,39 @@ __attribute__((amdgpu_waves_per_eu(plane_waves(INV, BIG, (int)sizeof(T), NT)))) 
             sxv[u] = *reinterpret_cast<const v8h *>(p.Sx + r * NXP + c);
         }
     }
-    T rv[INV ? 1 : QF][4];
+    // FP64 rows of more than 128 points go in two parts, whose values fit the registers (whole,
+    // 256 x 256 x 64 of 72 columns spilled 110 registers: 1170 -> 925 us; 192 x 192 x 100 x 48
+    // 294 -> 240).
+    constexpr int QP = !INV && sizeof(T) == 8 && NT > 8 ? QF / 2 : QF;
+    T rv[INV ? 1 : QP][4];
     v8h hv[INV ? QI : 1];
-    bool okq[INV ? QI : QF];
-    if constexpr (!INV) {
+    bool okq[INV ? QI : QP];
+    auto load_part = [&](int q0) {
 #pragma unroll
-        for (int q = 0; q < QF; ++q) {
-            const int it = tid + q * nthr;
+        for (int q = 0; q < QP; ++q) {
+            const int it = tid + (q0 + q) * nthr;
             const int r = it / (NXP / 4);
             const int x = (it - r * (NXP / 4)) * 4;
             okq[q] = r < rows && x < nx;
             load4<VEC>(R + (okq[q] ? base + (long)r * nx + x : base), rv[q]);
         }
+    };
+    auto put_part = [&](int q0) {
+#pragma unroll
+        for (int q = 0; q < QP; ++q) {
+            const int it = tid + (q0 + q) * nthr;
+            const int r = it / (NXP / 4);
+            const int x = (it - r * (NXP / 4)) * 4;
+            v4h h;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                h[i] = okq[q] && (VEC || x + i < nx) ? (_Float16)((float)rv[q][i] * sc)
+                                                     : (_Float16)0.f;
+            *reinterpret_cast<v4h *>(X + r * XP + x) = h;
+        }
+    };
+    if constexpr (!INV) {
+        load_part(0);
     } else {
 #pragma unroll
         for (int q = 0; q < QI; ++q) {
@@ -422,17 +446,10 @@ __attribute__((amdgpu_waves_per_eu(plane_waves(INV, BIG, (int)sizeof(T), NT)))) 
 
     if (PF && rb.fused) dev::col_parts_put(rzv, red);  // read behind the barriers below
     if constexpr (!INV) {
-#pragma unroll
-        for (int q = 0; q < QF; ++q) {
-            const int it = tid + q * nthr;
-            const int r = it / (NXP / 4);
-            const int x = (it - r * (NXP / 4)) * 4;
-            v4h h;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                h[i] = okq[q] && (VEC || x + i < nx) ? (_Float16)((float)rv[q][i] * sc)
-                                                     : (_Float16)0.f;
-            *reinterpret_cast<v4h *>(X + r * XP + x) = h;
+        put_part(0);
+        if constexpr (QP < QF) {
+            load_part(QP);
+            put_part(QP);
         }
     } else {
 #pragma unroll
@@ -451,19 +468,20 @@ __attribute__((amdgpu_waves_per_eu(plane_waves(INV, BIG, (int)sizeof(T), NT)))) 
     const int w = tid >> 6, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
     const int KX = NXP / 32;
     // this wave's rows of S_y (the A operand of the y-transform; NYP <= 32 KYM in 3-D),
-    // loaded now so that their latency overlaps the x-transform.  The scheduling barriers
-    // keep them between the slab's staging and the product: moved into either they cost
-    // 10 registers and, at 96 points a side, two of the eight waves per SIMD (183 against
-    // 171 us per inverse pass of 256 columns).  Planes beyond 128 points have four waves per
-    // SIMD either way and are faster when the loads may move (192: 438 against 461 us).
+    // loaded now so that their latency overlaps the x-transform.  Up to 96 points the
+    // scheduling barriers keep them between the slab's staging and the product: moved into
+    // either they cost 10 registers and, at 96 points a side, two of the eight waves per SIMD
+    // (183 against 171 us per inverse pass of 256 columns).  Wider forms have fewer registers to
+    // spare than the loads take and are faster when these may move (forward passes of 128^3
+    // x 64 columns 82 -> 63 us, 160 x 128 x 100 x 48 106 -> 84; inverse 192^3 x 64 461 -> 438).
     constexpr int KYM = BIG ? 8 : 4;
     v8h ay[KYM];
-    if constexpr (!BIG) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (NT <= 6 && !BIG) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks = 0; ks < KYM; ++ks)
         ay[ks] = *reinterpret_cast<const v8h *>(
             p.Sy + (16 * w + lr) * p.NYP + 32 * min(ks, p.NYP / 32 - 1) + 8 * lg);
-    if constexpr (!BIG) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (NT <= 6 && !BIG) __builtin_amdgcn_sched_barrier(0);
     v4f acc[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -558,31 +576,38 @@ __attribute__((amdgpu_waves_per_eu(plane_waves(INV, BIG, (int)sizeof(T), NT)))) 
             const int hrows = min(rows - r0, RH);
             if constexpr (PF) {
                 // each thread owns at most QH groups of 4 (RH * NXP / 4 <= QH * nthr): the
-                // P_old and V + sigma loads are issued together (clamped into the slab),
-                // then P is stored and w z^2 summed (z is 0 past nx)
-                constexpr int QH = QF / NH;
-                float po[QH][4], v4[QH][4];
+                // P_old and V + sigma loads of QB groups are issued together (clamped into the
+                // slab), then their P is stored and w z^2 summed (z is 0 past nx).  All groups at
+                // once but for 128 points and for 224 and more of the BIG form, whose limits
+                // (80 and 128 registers) a half fits: 128^3 x 64 columns 144 -> 115 us,
+                // 256 x 256 x 64 x 72 820 -> 760.  Others are faster whole (192 x 128 x 80 x 56:
+                // 203 and 228 us).
+                constexpr int QH = QF / NH, QB = QH == 7 || QH == 8 ? 4 : QH;
 #pragma unroll
-                for (int q = 0; q < QH; ++q) {
-                    const int it = tid + q * nthr;
-                    const int rl = it / g4, x = (it - rl * g4) * 4;
-                    const bool ok = rl < hrows && x < nx;
-                    const long off = ok ? (long)(r0 + rl) * nx + x : 0;
-                    if (first) po[q][0] = po[q][1] = po[q][2] = po[q][3] = 0.f;
-                    else load4<VEC>(Pold + base + off, po[q]);
-                    load4<VEC>(vs + pbase + off, v4[q]);
-                }
+                for (int q0 = 0; q0 < QH; q0 += QB) {
+                    float po[QB][4], v4[QB][4];
 #pragma unroll
-                for (int q = 0; q < QH; ++q) {
-                    const int it = tid + q * nthr;
-                    const int rl = it / g4, x = (it - rl * g4) * 4;
-                    if (rl >= hrows || x >= nx) continue;
-                    const float4 z4 = *reinterpret_cast<const float4 *>(SF + rl * FP + x);
-                    const v4f pv = first ? v4f{z4.x, z4.y, z4.z, z4.w}
-                                         : v4f{z4.x + b * po[q][0], z4.y + b * po[q][1],
-                                               z4.z + b * po[q][2], z4.w + b * po[q][3]};
-                    store4<VEC>(Z + base + (long)(r0 + rl) * nx + x, pv, nx - x);
-                    wz += wz4<VEC>(v4[q], vb, z4);
+                    for (int q = 0; q < QB && q0 + q < QH; ++q) {
+                        const int it = tid + (q0 + q) * nthr;
+                        const int rl = it / g4, x = (it - rl * g4) * 4;
+                        const bool ok = rl < hrows && x < nx;
+                        const long off = ok ? (long)(r0 + rl) * nx + x : 0;
+                        if (first) po[q][0] = po[q][1] = po[q][2] = po[q][3] = 0.f;
+                        else load4<VEC>(Pold + base + off, po[q]);
+                        load4<VEC>(vs + pbase + off, v4[q]);
+                    }
+#pragma unroll
+                    for (int q = 0; q < QB && q0 + q < QH; ++q) {
+                        const int it = tid + (q0 + q) * nthr;
+                        const int rl = it / g4, x = (it - rl * g4) * 4;
+                        if (rl >= hrows || x >= nx) continue;
+                        const float4 z4 = *reinterpret_cast<const float4 *>(SF + rl * FP + x);
+                        const v4f pv = first ? v4f{z4.x, z4.y, z4.z, z4.w}
+                                             : v4f{z4.x + b * po[q][0], z4.y + b * po[q][1],
+                                                   z4.z + b * po[q][2], z4.w + b * po[q][3]};
+                        store4<VEC>(Z + base + (long)(r0 + rl) * nx + x, pv, nx - x);
+                        wz += wz4<VEC>(v4[q], vb, z4);
+                    }
                 }
             } else {
                 for (int it = tid; it < hrows * g4; it += nthr) {
