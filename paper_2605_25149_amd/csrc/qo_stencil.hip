@@ -79,14 +79,31 @@ __device__ __forceinline__ bool engine_wide(const Grid &g, int band, int zc,
     ER er[PPT];
     LR hlo = Ld::zero(), hhi = Ld::zero();
     const long b0 = (long)z0 * plane + (long)y0 * nx;
+    // The operands' raw values are requested before pre(), unless they are three FP64 arrays at
+    // eight points per thread: 280 registers and one wave per SIMD instead of 217 and two
+    // (Jacobi first sweep of 256 x 256 x 64 columns 56 against 46 us, of 128 x 128 x 64 x 16 117
+    // against 106; every other form is faster with them in flight, sweeps by a fifth to a third).
+    constexpr bool kLate = PPT * sizeof(LR) >= 192;
     // operands of planes z0-1, z0 (with halo rows), z0+1
     LR rm[PPT], rc[PPT], rp[PPT], rlo = Ld::zero(), rhi = Ld::zero();
+    if constexpr (kLate) {
+        if (!pre()) return false;
 #pragma unroll
-    for (int s = 0; s < PPT; ++s) {
-        const int t = tid + s * kThreads;
-        rm[s] = (val[s] && z0 > 0) ? ld.load(b0 - plane + t) : Ld::zero();
-        rc[s] = val[s] ? ld.load(b0 + t) : Ld::zero();
-        rp[s] = (val[s] && z0 + 1 < nz) ? ld.load(b0 + plane + t) : Ld::zero();
+        for (int s = 0; s < PPT; ++s) {
+            const int t = tid + s * kThreads;
+            om[s] = (val[s] && z0 > 0) ? ld.make(ld.load(b0 - plane + t)) : T(0);
+            oc[s] = val[s] ? ld.make(ld.load(b0 + t)) : T(0);
+            op[s] = (val[s] && z0 + 1 < nz) ? ld.make(ld.load(b0 + plane + t)) : T(0);
+            if (val[s]) lds[nx + t] = oc[s];
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < PPT; ++s) {
+            const int t = tid + s * kThreads;
+            rm[s] = (val[s] && z0 > 0) ? ld.load(b0 - plane + t) : Ld::zero();
+            rc[s] = val[s] ? ld.load(b0 + t) : Ld::zero();
+            rp[s] = (val[s] && z0 + 1 < nz) ? ld.load(b0 + plane + t) : Ld::zero();
+        }
     }
     if (hown && has_lo) rlo = ld.load(b0 + lo_off + tid);
     if (hown && has_hi) rhi = ld.load(b0 + hi_off + tid);
@@ -102,14 +119,16 @@ __device__ __forceinline__ bool engine_wide(const Grid &g, int band, int zc,
         if (has_lo) hlo = ld.load(b0 + plane + lo_off + tid);
         if (has_hi) hhi = ld.load(b0 + plane + hi_off + tid);
     }
-    if (!pre()) return false;
+    if constexpr (!kLate) {
+        if (!pre()) return false;
 #pragma unroll
-    for (int s = 0; s < PPT; ++s) {
-        const int t = tid + s * kThreads;
-        om[s] = (val[s] && z0 > 0) ? ld.make(rm[s]) : T(0);
-        oc[s] = val[s] ? ld.make(rc[s]) : T(0);
-        op[s] = (val[s] && z0 + 1 < nz) ? ld.make(rp[s]) : T(0);
-        if (val[s]) lds[nx + t] = oc[s];
+        for (int s = 0; s < PPT; ++s) {
+            const int t = tid + s * kThreads;
+            om[s] = (val[s] && z0 > 0) ? ld.make(rm[s]) : T(0);
+            oc[s] = val[s] ? ld.make(rc[s]) : T(0);
+            op[s] = (val[s] && z0 + 1 < nz) ? ld.make(rp[s]) : T(0);
+            if (val[s]) lds[nx + t] = oc[s];
+        }
     }
     if (hown) {
         lds[tid] = has_lo ? ld.make(rlo) : T(0);
@@ -624,15 +643,14 @@ __global__ __launch_bounds__(kThreads) void k_resid_next(Grid g, const double *_
 // columns with mask != 0, r = b - H x in FP64, r32 = (float) r.  Partials in the
 // FP32 PCG layout: q0 = r32 . D32 r32, q1 = q2 = ||r32||^2; and in `outer`:
 // [0] ||r||^2 (FP64), [1] ||b||^2.  Unmasked columns are untouched.
+// Held to 128 registers at 3 points per thread, where it takes 129 by itself and loses a wave
+// per SIMD (96^3 x 32 columns: 46.4 against 44.4 us).
 template <int PPT>
-__global__ __launch_bounds__(kThreads) void k_resid_rel(Grid g, const double *__restrict__ vs,
-                                                        const float *__restrict__ dinv32,
-                                                        const double *__restrict__ B,
-                                                        const double *__restrict__ X, long ld,
-                                                        float *__restrict__ R32,
-                                                        const int *__restrict__ mask,
-                                                        double *__restrict__ part, long qs,
-                                                        double *__restrict__ outer) {
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(PPT == 3 ? 4 : 1))) void k_resid_rel(
+    Grid g, const double *__restrict__ vs, const float *__restrict__ dinv32,
+    const double *__restrict__ B, const double *__restrict__ X, long ld, float *__restrict__ R32,
+    const int *__restrict__ mask, double *__restrict__ part, long qs, double *__restrict__ outer) {
     __shared__ Red red;
     int col, tile, band, zc;
     tile_of(g, col, tile, band, zc);

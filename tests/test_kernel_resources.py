@@ -86,3 +86,11 @@ def test_plane_pass_occupancy(kernels):
             limit = 256
         for total, _ in regs:
             assert total <= limit, (form, regs)
+
+
+@pytest.mark.parametrize("form,limit", [("k_pcg_sweep1IdLi8ELb0EE", 256), ("k_resid_relILi3EE", 128)])
+def test_stencil_occupancy(kernels, form, limit):
+    """The Jacobi first sweep of eight points per thread in FP64 keeps two wavefronts per SIMD,
+    the residual replacement of three points four."""
+    found = [v for name, v in kernels.items() if form in name]
+    assert found and all(total <= limit and spilled == 0 for total, spilled in found), found
