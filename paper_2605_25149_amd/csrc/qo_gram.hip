@@ -62,12 +62,16 @@ __device__ __forceinline__ void tile_pair(int p, int nt, int &ti, int &tj) {
 
 // One wavefront's rows [kb, ke) of a tile of NI x NJ blocks of 16 x 16 (DIAG: a diagonal
 // tile, whose operands coincide and whose blocks below the diagonal are left out): acc is
-// left in LDS layout order, slot 4 i + j.  VEC: 16-byte aligned columns.
-template <int NI, int NJ, bool DIAG, bool VEC, int W>
+// left in LDS layout order, slot 4 i + j.  VEC: 16-byte aligned columns; kVecRuntime: by vec_ok,
+// for the 4 x 4 form of a kernel that holds no other: its two loops then share one end, and the
+// compiler leaves acc in the accumulation registers (one copy of the form for each
+// alignment moved eight of them to and fro in every iteration).
+enum { kVecNo, kVecYes, kVecRuntime };
+template <int NI, int NJ, bool DIAG, int VEC, int W>
 __device__ __forceinline__ void gram_rows(const double *const (&pa_)[4],
                                           const double *const (&pb_)[4], long kb, long ke,
                                           double *__restrict__ red, double *__restrict__ out,
-                                          int wave, int nn, int r0t, int c0t) {
+                                          int wave, int nn, int r0t, int c0t, int vec_ok) {
     constexpr int NB = DIAG ? 1 : NJ;  // column groups of B loaded
     static_assert(W == 1 || W == 4, "W = 4: one value of a block per wavefront in the final sum");
     const int lr = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4;
@@ -92,30 +96,42 @@ __device__ __forceinline__ void gram_rows(const double *const (&pa_)[4],
                         a[i][s], DIAG ? a[j < NI ? j : 0][s] : b[j < NB ? j : 0][s], acc[i][j], 0,
                         0, 0);
     };
-    auto load4 = [&](gdouble *p, long r0, double (&v)[4]) {
-        if constexpr (VEC) {
-            gd2 *q = (gd2 *)(p + r0);
-            const d2 v0 = q[0], v1 = q[1];
-            v[0] = v0.x; v[1] = v0.y; v[2] = v1.x; v[3] = v1.y;
-        } else {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) v[s] = p[r0 + s];
-        }
-    };
-    auto load_chunk = [&](long k0, double (&a)[NI][4], double (&b)[NB][4]) {
-        const long r0 = k0 + 4 * lg;
-#pragma unroll
-        for (int i = 0; i < NI; ++i) load4(pa[i], r0, a[i]);
-        if constexpr (!DIAG)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) load4(pb[j], r0, b[j]);
-    };
-    // full chunks of 16 rows, software-pipelined one chunk ahead (past the end the prefetch
-    // re-reads the final chunk); the scheduling barriers keep the prefetch ahead of the MFMAs
-    // it overlaps
     const long len = ke > kb ? ke - kb : 0;
     const long kend = kb + (len & ~15L);
-    if (kend > kb) {
+    auto main_loop = [&](auto vec) {
+        auto load4 = [&](gdouble *p, long r0, double (&v)[4]) {
+            if constexpr (decltype(vec)::value) {
+                gd2 *q = (gd2 *)(p + r0);
+                const d2 v0 = q[0], v1 = q[1];
+                v[0] = v0.x; v[1] = v0.y; v[2] = v1.x; v[3] = v1.y;
+            } else {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) v[s] = p[r0 + s];
+            }
+        };
+        auto load_chunk = [&](long k0, double (&a)[NI][4], double (&b)[NB][4]) {
+            const long r0 = k0 + 4 * lg;
+            if constexpr (VEC == kVecRuntime) {
+                // one wavefront per SIMD: in turn, so that the first products wait for the
+                // first few loads alone (all of a before b: 512 columns at 96^3 rows 4.50
+                // instead of 4.39 ms)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    load4(pa[i], r0, a[i]);
+                    load4(pb[i], r0, b[i]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < NI; ++i) load4(pa[i], r0, a[i]);
+                if constexpr (!DIAG)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) load4(pb[j], r0, b[j]);
+            }
+        };
+        // full chunks of 16 rows, software-pipelined one chunk ahead (past the end the
+        // prefetch re-reads the final chunk); the scheduling barriers keep the prefetch ahead
+        // of the MFMAs it overlaps
+        if (kend <= kb) return;
         double a0[NI][4], b0[NB][4], a1[NI][4], b1[NB][4];
         const long last = kend - 16;
         const long npairs = (kend - kb) >> 5;
@@ -132,6 +148,12 @@ __device__ __forceinline__ void gram_rows(const double *const (&pa_)[4],
             __builtin_amdgcn_sched_barrier(0);
         }
         if ((kend - kb) & 16) mma_chunk(a0, b0);
+    };
+    if constexpr (VEC == kVecRuntime) {
+        if (vec_ok) main_loop(std::true_type{});
+        else main_loop(std::false_type{});
+    } else {
+        main_loop(std::bool_constant<VEC == kVecYes>{});
     }
     // tail rows [kend, ke): rows past ke are zeroed (they belong to another chunk)
     if (kend < ke) {
@@ -204,14 +226,15 @@ __device__ __forceinline__ void gram_rows(const double *const (&pa_)[4],
 // chunk costs one partial instead of one per wavefront (with one wavefront per chunk the
 // partials of 96 columns at 64^3 rows were 75 MB written and read against 201 MB of
 // operands).  W = 1 (many tile pairs): the wavefronts of a CU are different tile pairs of
-// the same rows and share them in the caches (512 columns at 96^3 rows: 4.60 ms with
+// the same rows and share them in the caches (512 columns at 96^3 rows: 4.38 ms, 4.84 with
 // W = 4).  16 x 16 blocks past the last column, or below the diagonal of a diagonal tile,
 // are not computed (an FP64 MFMA occupies its matrix core for 64 cycles, and with 96 columns
 // 27 of 48 blocks are of that kind): the tile's extent selects a form whose loops hold its
-// blocks alone.
+// blocks alone.  WHOLE (kGramTilesWhole tiles a side and more, W = 1): every tile is computed
+// whole, in a kernel of that form alone.
 // CROSS: the n x n block X^T Y alone (tile (ti, tj) = pair / ntn, pair % ntn over X
 // columns x Y columns), partials n x n per split.
-template <int W, bool CROSS = false>
+template <int W, bool CROSS = false, bool WHOLE = false>
 __device__ __forceinline__ void gram_f64_tile(const double *__restrict__ X,
                                               const double *__restrict__ Y, long ld, long ng,
                                               int n, long kchunk, double *__restrict__ part,
@@ -256,31 +279,29 @@ __device__ __forceinline__ void gram_f64_tile(const double *__restrict__ X,
     // column blocks of the tile; its row blocks are 4 off the diagonal of the symmetric
     // Gram (only the last tile is cut), unaligned operands take the whole tile
     const int nj = min(4, (nn - c0 + 15) / 16);
-#define QO_GRAM(NI, NJ, D, V) gram_rows<NI, NJ, D, V, W>(pa, pb, kb, ke, red, out, wave, nn, r0, c0)
-    if (!vec_ok) {
-        if (!CROSS && ti == tj) QO_GRAM(4, 4, true, false);
-        else QO_GRAM(4, 4, false, false);
+#define QO_GRAM(NI, NJ, D, V) gram_rows<NI, NJ, D, V, W>(pa, pb, kb, ke, red, out, wave, nn, r0, c0, vec_ok)
+    if constexpr (WHOLE || (CROSS && W == 1)) {
+        QO_GRAM(4, 4, false, kVecRuntime);
+    } else if (!vec_ok) {
+        if (!CROSS && ti == tj) QO_GRAM(4, 4, true, kVecNo);
+        else QO_GRAM(4, 4, false, kVecNo);
     } else if (CROSS) {
-        QO_GRAM(4, 4, false, true);
-    } else if (ti == tj && (W != 1 || nt < 7)) {
-        // From 28 tile pairs on (W = 1) diagonal tiles are computed whole: their wavefronts
-        // would run ahead of the others on the same rows, which then meet in the caches less
-        // often (trimmed against whole, 512 columns at 96^3 rows: 4.81 and 4.59 ms; with 15
-        // pairs the work saved weighs more, 320 columns at 64^3 rows: 0.76 and 0.81 ms).
-        if (nj == 4) QO_GRAM(4, 4, true, true);
-        else if (nj == 3) QO_GRAM(3, 3, true, true);
-        else if (nj == 2) QO_GRAM(2, 2, true, true);
-        else QO_GRAM(1, 1, true, true);
+        QO_GRAM(4, 4, false, kVecYes);
+    } else if (ti == tj) {
+        if (nj == 4) QO_GRAM(4, 4, true, kVecYes);
+        else if (nj == 3) QO_GRAM(3, 3, true, kVecYes);
+        else if (nj == 2) QO_GRAM(2, 2, true, kVecYes);
+        else QO_GRAM(1, 1, true, kVecYes);
     } else {
-        if (nj == 4) QO_GRAM(4, 4, false, true);
-        else if (nj == 3) QO_GRAM(4, 3, false, true);
-        else if (nj == 2) QO_GRAM(4, 2, false, true);
-        else QO_GRAM(4, 1, false, true);
+        if (nj == 4) QO_GRAM(4, 4, false, kVecYes);
+        else if (nj == 3) QO_GRAM(4, 3, false, kVecYes);
+        else if (nj == 2) QO_GRAM(4, 2, false, kVecYes);
+        else QO_GRAM(4, 1, false, kVecYes);
     }
 #undef QO_GRAM
 }
 
-template <int W>
+template <int W, bool WHOLE = false>
 __global__ __launch_bounds__(64 * W) void k_gram_f64(const double *__restrict__ X,
                                                  const double *__restrict__ Y, long ld, long ng,
                                                  int n, long kchunk, double *__restrict__ part,
@@ -291,7 +312,8 @@ __global__ __launch_bounds__(64 * W) void k_gram_f64(const double *__restrict__ 
     const int npairs = nt * (nt + 1) / 2;
     const int L = xcd_remap(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     const int split = L / npairs;
-    gram_f64_tile<W>(X, Y, ld, ng, n, kchunk, part, vec_ok, L - split * npairs, split, red);
+    gram_f64_tile<W, false, WHOLE>(X, Y, ld, ng, n, kchunk, part, vec_ok, L - split * npairs, split,
+                                   red);
 }
 
 template <int W>
@@ -587,6 +609,13 @@ int gram_nsplit(long ng, int n) {
 // round is not nearly empty, and at least 256 rows each (four 16-row steps per wavefront).
 // More pairs: one wavefront and all the chunks, which share their operands' rows.
 constexpr int kGramPairsW4 = 10;
+// Tiles a side from which they are computed whole: trimmed ones would run ahead of the
+// others on the same rows, which then meet in the caches less often (whole against trimmed:
+// 512 columns at 96^3 rows 4.38 and 4.70 ms, 480 columns 4.26 and 4.61, 512 columns at
+// 64^3 rows 1.68 and 1.64; with six tiles the work saved weighs as much, 384 columns
+// 2.61 and 2.71 ms at 96^3 rows, 0.98 and 0.92 at 64^3, and with five more, 300 columns at 64^3
+// 0.69 and 0.65).
+constexpr int kGramTilesWhole = 7;
 constexpr long kGramTarget = 1024;
 static int gram_f64_waves(int npairs) { return npairs <= kGramPairsW4 ? kGramWaves : 1; }
 static int gram_f64_nsplit(int npairs, long ng, int most) {
@@ -615,7 +644,10 @@ hipError_t launch_gram_f64(const double *X, const double *Y, long ld, long ng, i
     kchunk = (kchunk + 31) / 32 * 32;
     const int vec_ok = (ld % 2 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0) &&
                        ((reinterpret_cast<uintptr_t>(Y) & 15) == 0);
-    if (gram_f64_waves(npairs) == 1)
+    if (nt >= kGramTilesWhole)
+        hipLaunchKernelGGL((k_gram_f64<1, true>), dim3(npairs, nsplit), dim3(64), 0, st, X, Y, ld, ng, n,
+                           kchunk, part, vec_ok);
+    else if (gram_f64_waves(npairs) == 1)
         hipLaunchKernelGGL(k_gram_f64<1>, dim3(npairs, nsplit), dim3(64), 0, st, X, Y, ld, ng, n,
                            kchunk, part, vec_ok);
     else

@@ -94,3 +94,11 @@ def test_stencil_occupancy(kernels, form, limit):
     the residual replacement of three points four."""
     found = [v for name, v in kernels.items() if form in name]
     assert found and all(total <= limit and spilled == 0 for total, spilled in found), found
+
+
+@pytest.mark.parametrize("form,limit", [("k_gram_f64ILi1ELb1EE", 300), ("k_gram_cross_f64ILi1EE", 316)])
+def test_gram_registers(kernels, form, limit):
+    """One-wavefront FP64 Gram kernels of many tiles: with more registers than these (128 of them
+    for accumulation) the compiler moves accumulators in and out in every iteration."""
+    found = [v for name, v in kernels.items() if form in name]
+    assert found and all(total <= limit and spilled == 0 for total, spilled in found), found
