@@ -51,7 +51,7 @@ struct qo_batch_ctx {
         DstPlan dp{};
         bool dst = false;
         long ng = 0, ld = 0, qs = 0;
-        int C = 0, kmax = 0, ninst = 0, max_n = 0, max_gram_grid = 0, ty = 0;
+        int C = 0, kmax = 0, ninst = 0, max_n = 0, max_gram_grid = 0, max_split = 0, ty = 0;
         int kuse = 0;  // iterations per solve in use: kmax until counts are observed
         // mixed precision: FP32 PCG inside restarted FP64 refinement rounds
         bool mixed = false;
@@ -313,13 +313,15 @@ qo_status group_step_enqueue(qo_batch_ctx *b, qo_batch_ctx::Group &G, int par) {
     double *P = G.PQ[par], *Q = G.PQ[par ^ 1];
     if (G.mixed) BQO(group_solve_mixed(b, G, G.U, P, 0));
     else BQO(group_pcg(b, G, G.U, P, 0));
-    BHIP(b, launch_gram_f64_batch(G.gjob[par][0], G.ninst, G.max_gram_grid, G.ld, G.ng, G.w, st));
+    BHIP(b, launch_gram_f64_batch(G.gjob[par][0], G.ninst, G.max_gram_grid, G.max_n, G.max_split,
+                                  G.ld, G.ng, G.w, st));
     BHIP(b, launch_nn_predict(G.njob, G.ninst, G.max_n, st));
     BHIP(b, launch_tsgemm_batch(G.tjob[par][0], G.ninst, G.max_n, G.ld, G.ng, st));
     BHIP(b, launch_tsgemm_batch(G.tjob[par][1], G.ninst, G.max_n, G.ld, G.ng, st));
     if (G.mixed) BQO(group_solve_mixed(b, G, G.Uh, Q, 1));
     else BQO(group_pcg(b, G, G.Uh, Q, 1));
-    BHIP(b, launch_gram_f64_batch(G.gjob[par][1], G.ninst, G.max_gram_grid, G.ld, G.ng, G.w, st));
+    BHIP(b, launch_gram_f64_batch(G.gjob[par][1], G.ninst, G.max_gram_grid, G.max_n, G.max_split,
+                                  G.ld, G.ng, G.w, st));
     BHIP(b, launch_nn_correct(G.njob, G.ninst, G.max_n, st));
     BHIP(b, launch_tsgemm_batch(G.tjob[par][2], G.ninst, G.max_n, G.ld, G.ng, st));
     BHIP(b, launch_quad(G.g, G.vs, G.U, G.ld, G.C, G.part, st));
@@ -503,6 +505,7 @@ qo_status build_group(qo_batch_ctx *b, qo_batch_ctx::Group &G) {
         g_tot += (size_t)4 * n * n;
         gp_tot += gram_part_elems(n, nsplit[li]);
         G.max_gram_grid = std::max(G.max_gram_grid, gram_pairs(n) * nsplit[li]);
+        G.max_split = std::max(G.max_split, nsplit[li]);
     }
     BQO(A(&G.pool, pool_tot));
     BQO(A(&G.G1, g_tot));

@@ -529,7 +529,9 @@ __global__ __launch_bounds__(1024) void k_gram_bf16_super(const __bf16 *__restri
 }
 
 // G[r][c] = w * sum_s part[s][min(r,c)][max(r,c)], 64 entries from 64 chunk on: each entry
-// with r <= c is summed once and gives both G[r][c] and G[c][r].
+// with r <= c is summed once and gives both G[r][c] and G[c][r].  FEW: by one wavefront, each
+// entry's partials in turn (the same sum for up to kRedWaves of them).
+template <bool FEW = false>
 __device__ __forceinline__ void gram_reduce_chunk(const double *__restrict__ part, int nn,
                                                   int nsplit, double w, double *__restrict__ G,
                                                   long chunk, double *__restrict__ sh) {
@@ -537,8 +539,15 @@ __device__ __forceinline__ void gram_reduce_chunk(const double *__restrict__ par
     const long e = chunk * 64 + (threadIdx.x & 63);
     const int c = (int)(e / nn), r = (int)(e - (long)c * nn);
     const bool mine = e < total && r <= c;
-    const double s = sum_parts(part, total, nsplit, mine ? e : total, sh);
-    if (threadIdx.x < 64 && mine) {
+    double s = 0.0;
+    if constexpr (FEW) {
+        if (mine)
+#pragma unroll 8
+            for (int k = 0; k < nsplit; ++k) s += part[(long)k * total + e];
+    } else {
+        s = sum_parts(part, total, nsplit, mine ? e : total, sh);
+    }
+    if ((FEW || threadIdx.x < 64) && mine) {
         G[e] = w * s;
         G[(long)r * nn + c] = w * s;
     }
@@ -563,18 +572,40 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_gram_reduce_batch(
     }
 }
 
+// ... with at most kFewParts partials per instance: four chunks per workgroup.
+__global__ __launch_bounds__(256) void k_gram_reduce_batch_few(const GramJob *__restrict__ jobs,
+                                                               double w) {
+    const GramJob J = jobs[blockIdx.z];
+    const int nn = 2 * J.n;
+    const long chunks = ((long)nn * nn + 63) / 64;
+    for (long ch = blockIdx.x * 4L + (threadIdx.x >> 6); ch < chunks; ch += 4L * gridDim.x)
+        gram_reduce_chunk<true>(J.part, nn, J.nsplit, w, J.G, ch, nullptr);
+}
+
 }  // namespace
 
-hipError_t launch_gram_f64_batch(const GramJob *jobs, int njobs, int max_grid, long ld, long ng,
-                                 double w, hipStream_t st) {
+// Batches of many instances have few partials each (about 2048 workgroups are shared out over
+// the group): sixteen wavefronts for one partial, 128 workgroups for every instance, cost 1000
+// instances of 4 columns 137 us a reduction and 512 of 8 columns 72; a wavefront per 64
+// entries, and no more workgroups than entries need, 4.9 and 4.8.
+constexpr int kFewParts = 8;
+hipError_t launch_gram_f64_batch(const GramJob *jobs, int njobs, int max_grid, int max_n,
+                                 int max_split, long ld, long ng, double w, hipStream_t st) {
     if (njobs <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_gram_f64_batch, dim3((unsigned)max_grid, 1, (unsigned)njobs),
                        dim3(64 * kGramWaves), kGramLds,
                        st, jobs, ld, ng, 1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gram_reduce_batch, dim3(128, 1, (unsigned)njobs), dim3(64 * kRedWaves), 0,
-                       st, jobs, w);
+    const long chunks = (4L * max_n * max_n + 63) / 64;
+    if (max_split <= kFewParts)
+        hipLaunchKernelGGL(k_gram_reduce_batch_few,
+                           dim3((unsigned)std::min(128L, (chunks + 3) / 4), 1, (unsigned)njobs),
+                           dim3(256), 0, st, jobs, w);
+    else
+        hipLaunchKernelGGL(k_gram_reduce_batch,
+                           dim3((unsigned)std::min(128L, chunks), 1, (unsigned)njobs),
+                           dim3(64 * kRedWaves), 0, st, jobs, w);
     return hipGetLastError();
 }
 

@@ -327,8 +327,8 @@ struct GramJob {
 };
 int gram_pairs(int n);
 long gram_kchunk(long ng, int nsplit);
-hipError_t launch_gram_f64_batch(const GramJob *jobs, int njobs, int max_grid, long ld, long ng,
-                                 double w, hipStream_t st);
+hipError_t launch_gram_f64_batch(const GramJob *jobs, int njobs, int max_grid, int max_n,
+                                 int max_split, long ld, long ng, double w, hipStream_t st);
 
 // ---- grouped batches: N x N algebra per instance (qo_batch.hip) ----
 struct NnJob {
