@@ -293,8 +293,10 @@ qo_status qo_get_matrix(qo_handle h, int which, double *out);
  * instance's group to the counts of a fresh batch (pcg_maxit; six rounds in mixed
  * precision) and drop its captured graphs, since a cold start or a new operator needs
  * more iterations than the warm-started steps before it; a step that fails with
- * QO_ERR_PCG_NOCONV does the same for every group.  With use_graph != 0 each step is replayed from a HIP graph
- * captured at its first use (one per parity of the P / Q buffers); the stream given to
+ * QO_ERR_PCG_NOCONV does the same for every group.  With use_graph != 0 each step is
+ * replayed from a HIP graph captured at its first use (one per parity of the P / Q
+ * buffers); steps of more than 50000 launches, as pcg_maxit may ask for until counts are
+ * observed, are enqueued directly.  With use_graph the stream given to
  * qo_batch_create must then not be the null stream (NULL creates a private stream).  At
  * creation the band height of the stencil kernels is chosen per group by timing the
  * candidates on the device (qo_batch_tile reports it).  A failed step leaves the states

@@ -355,6 +355,27 @@ qo_status batch_step_enqueue(qo_batch_ctx *b, int par) {
     return first;
 }
 
+// Kernel launches of one step at the counts in use, PCG iterations alone (the rest is a few
+// dozen per group).
+long step_launches(const qo_batch_ctx *b) {
+    long n = 0;
+    for (const auto &G : b->groups) {
+        long its = 0;  // of both solves
+        if (G.mixed)
+            for (int r = 0; r < G.ruse; ++r) its += 2 * (G.kr[r] + 1L);
+        else
+            its = 2 * (G.kuse + 1L);
+        n += its * (G.dst ? 6 : 2);
+    }
+    return n;
+}
+
+// Steps of more launches than this are enqueued directly instead of captured: until counts have
+// been observed a solve runs pcg_maxit iterations, up to 100000.  Graphs of 80000 kernel nodes
+// in one chain have run; with one of 240000 (pcg_maxit 20000, fast-Poisson) the call ended in
+// a segmentation fault on the host.
+constexpr long kGraphLaunches = 50000;
+
 qo_status build_group(qo_batch_ctx *b, qo_batch_ctx::Group &G) {
     const qo_config &cf = G.cf;
     G.ninst = (int)G.members.size();
@@ -846,7 +867,7 @@ qo_status qo_batch_step(qo_batch b, const double *taus, int nsteps, int use_grap
     BHIP(b, hipStreamSynchronize(st));
     for (int step = 0; step < nsteps; ++step) {
         const int par = b->cur;
-        if (use_graph) {
+        if (use_graph && step_launches(b) <= kGraphLaunches) {
             if (!b->gvalid[par]) {
                 hipGraph_t graph = nullptr;
                 BHIP(b, hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
