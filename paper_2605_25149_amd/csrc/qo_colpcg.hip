@@ -1,21 +1,27 @@
-// FP64 Jacobi-PCG of small grids with a whole column per workgroup: the inverse operator
-// G = H_sigma^{-1} of Sec. 3.1 for grids of at most kColPcgMax points.
+// FP64 Jacobi-PCG that keeps its columns on the chip: the inverse operator
+// G = H_sigma^{-1} of Sec. 3.1 with a whole column per workgroup (k_pcg_column, grids of at most
+// kColPcgMax = 16384 points) or per cluster of up to kCluMaxW = 64 workgroups of at most
+// kCluPts = 8192 points each (k_pcg_cluster, up to 524288 points; second part of this file).
 //
 // The streaming form (qo_stencil.hip) takes two launches per iteration, each a chain of
 // flag loads, partial-sum reductions and plane passes of 5 to 6 us however small the grid;
-// a 32 x 32 solve of some 120 iterations then costs 1.9 ms.  Here one workgroup
-// keeps its column on the CU for the whole solve: x, r and the search direction in
-// registers, a copy of the direction in LDS for the neighbours, and the dot products as
-// wavefront sums exchanged through LDS.  An iteration is three barriers and touches
-// no global memory (above 8 points per thread x and the per-point arrays V + sigma and
-// 1/diag stay in L2, and the thread's own direction is read back from LDS).
-// Columns are independent, so a solve of N columns is one launch of N workgroups.
+// a 32 x 32 solve of some 120 iterations then costs 1.9 ms.
 //
-// Bound: latency of the two reductions on the smallest grids, LDS traffic (five accesses
-// per point in 2-D, seven in 3-D) and the FP64 rate of the column's CU on the larger ones,
-// the L2 round trips above 8192 points.  Measured times stand at the launch.
+// A workgroup per column: it keeps its column on the CU for the whole solve, x, r and the
+// search direction in registers, a copy of the direction in LDS for the neighbours, and
+// the dot products as wavefront sums exchanged through LDS.  An iteration is three barriers
+// and touches no global memory (above 8 points per thread x and the per-point arrays V + sigma
+// and 1/diag stay in L2, and the thread's own direction is read back from LDS).  Columns are
+// independent, so a solve of N columns is one launch of N workgroups.
 //
-// Same iteration, stop test and error conditions as the streaming form; the dot products
+// A cluster per column exchanges faces, partial sums and counters through global memory every
+// iteration and needs its workgroups on the chip together; what that takes stands with it.
+//
+// Bound of the first form: latency of the two reductions on the smallest grids, LDS traffic
+// (five accesses per point in 2-D, seven in 3-D) and the FP64 rate of the column's CU on the
+// larger ones, the L2 round trips above 8192 points.  Measured times stand at the launch.
+//
+// Both: same iteration, stop test and error conditions as the streaming form; the dot products
 // are summed in another order.
 #include "qo_device.h"
 #include "qo_internal.h"

@@ -222,7 +222,8 @@ hipError_t launch_pcg_sweep2(const Grid &g, const T *vs, const T *dinv, const T 
                              long ld, int ncols, int k, PcgState s, hipStream_t st,
                              bool jac = true, bool xzero = false);
 
-// ---- a column per workgroup (qo_colpcg.hip): FP64 Jacobi-PCG of small grids ----
+// ---- a column per workgroup or per cluster of workgroups (qo_colpcg.hip): FP64 Jacobi-PCG of
+// grids of at most 16384 or 524288 points ----
 // Iterations k0 .. kend of X = G B for ncols columns in one launch.  R, P (blocks) and scal
 // (4 ncols doubles) carry the columns still running from a launch to the next one from its
 // kend; last: there is none.  its[c] and state[c] (device-accessible) receive the iteration
